@@ -123,7 +123,8 @@ inline int64_t pack_a8_index(int64_t row, int64_t k, int64_t K) { return pack_w8
 // 16-bit operand GEMM on MFMA (K > 0, K % 32 == 0, lda % 8 == 0, 16-byte aligned
 // A, row-major or packed; W packed as above).
 hipError_t gemm_mfma(Act16 t, const GemmArgs& g, hipStream_t stream);
-// fp32 GEMM (any shape) for the fp32 compute path.
+// fp32 GEMM (any shape) for the fp32 compute path. EPI_SWIGLU: W rows are gate
+// rows 0 .. N/2 - 1, then up rows (not interleaved); out_a is fp32.
 hipError_t gemm_f32(const GemmArgs& g, hipStream_t stream);
 // E4M3 x E4M3 GEMM on the gfx950 32x32x64 FP8 MFMA: A [M, K] E4M3 bytes
 // row-major (lda bytes, lda % 16 == 0) or packed (a_packed, pack_a8_index),
@@ -182,9 +183,6 @@ hipError_t rope_time(const QkvPostArgs& a, hipStream_t stream);
 // (packed: 16-bit output in the packed operand layout, K = K_pad).
 hipError_t unshuffle_latent(const void* z, int z_kind, int B, int C, int F, int H, int W, int p,
                             int K_pad, void* u, int out_kind, hipStream_t stream, bool packed = false);
-
-// h[m, j] = SiLU(raw[m, j]) * raw[m, H + j]  (fp32 path, un-interleaved weights)
-hipError_t swiglu_f32(const float* raw, int M, int H, float* h, hipStream_t stream);
 
 // Sustained MFMA throughput probe: `blocks` workgroups of 4 waves issue 16
 // 32x32x16 MFMAs per iteration each; clk receives per workgroup the shader

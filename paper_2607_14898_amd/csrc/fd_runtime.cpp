@@ -594,20 +594,11 @@ fd_status run_stack(Ctx& x, const std::vector<LayerW>& layers, float* xs, int ro
     }
     if ((st = run_norm(x, xs, rows, w.n2g, w.n2b))) return st;
     if (c.mlp_kind == FD_MLP_SWIGLU) {
-      if (d.is16) {
-        g = gemm_args(kc->a, D, w.w1, rows, 2 * H, D, fd::EPI_SWIGLU, w.b1);
-        g.ep.sat = kc->sat;
-        g.ep.out_a = kc->h;
-        g.ep.ld_out = H;
-        if ((st = run_gemm(x, g, D))) return st;
-      } else {
-        g = gemm_args(kc->a, D, w.w1, rows, 2 * H, D, fd::EPI_STORE_F32, w.b1);
-        g.ep.out_f = kc->raw;
-        g.ep.ld_out = 2 * H;
-        if ((st = run_gemm(x, g, D))) return st;
-        e = fd::swiglu_f32(kc->raw, rows, H, (float*)kc->h, x.s);
-        if (e != hipSuccess) return fail(FD_ERR_DEVICE, "swiglu launch failed: %s", hipGetErrorString(e));
-      }
+      g = gemm_args(kc->a, D, w.w1, rows, 2 * H, D, fd::EPI_SWIGLU, w.b1);
+      g.ep.sat = kc->sat;
+      g.ep.out_a = kc->h;
+      g.ep.ld_out = H;
+      if ((st = run_gemm(x, g, D))) return st;
     } else {
       g = gemm_args(kc->a, D, w.w1, rows, H, D, fd::EPI_STORE_GELU, w.b1);
       g.ep.out_a = kc->h;

@@ -394,13 +394,24 @@ __global__ __launch_bounds__(256, NQB == 2 ? 2 : 3) void attn_mfma_kernel(AttnAr
   }
 }
 
-// fp32 path: one thread per query, 64 queries of one head per workgroup.
-template <int DH>
-__global__ __launch_bounds__(64) void attn_f32_kernel(AttnArgs a, int q_tiles) {
-  __shared__ float sk[64][DH + 1];
-  __shared__ float sv[DH][65];
-  __shared__ float ss[64][65];  // scores of a key tile, one column per thread (query)
-  const int tid = threadIdx.x;
+// fp32 path (D_h = 16, 32 or 64) on the 16x16x4 fp32 MFMA: a workgroup is one
+// head's tile of 16 NQ queries, and its 4 waves split the keys: wave w takes the
+// 16-key blocks w, w + 4, .. of the visible window, four at a time, with its own
+// running maximum and sums, and the four partial results meet in LDS. A wave
+// computes S^T = K Q^T, so lane (g, r) holds query r's scores of keys 4 g .. 4 g
+// + 3 of a block, which is exactly the B operand of the following O^T += V^T P^T
+// step by step; K, V^T and Q are read from memory as 16 bytes per lane (component
+// j is the operand of MFMA step j). A query's result does not depend on NQ.
+template <int DH, int NQ>
+__global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a, int q_tiles) {
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  constexpr int DC = DH / 16;  // 16-column chunks of a head vector
+  constexpr int KB = 4;        // key blocks per softmax step
+  __shared__ float so[4][NQ * 16][DH + 1];
+  __shared__ float sm[4][NQ * 16], sl[4][NQ * 16];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 15, lg = lane >> 4;
   const int n = blockIdx.y;
   const int bx = blockIdx.x;
   const int qt = bx % q_tiles, bu = bx / q_tiles;
@@ -408,50 +419,122 @@ __global__ __launch_bounds__(64) void attn_f32_kernel(AttnArgs a, int q_tiles) {
   const int g = n / (a.N / a.G);
   const int64_t u = a.u0 + lu;
   const int ldq = a.N * DH;
-  const int qi = qt * 64 + tid;
-  const int64_t qrow = (int64_t)(b * a.n_units + lu) * a.U + min(qi, a.U - 1);
-  float q[DH], o[DH];
-  for (int d = 0; d < DH; ++d) {
-    q[d] = ((const float*)a.q)[qrow * ldq + n * DH + d];
-    o[d] = 0.f;
+  const int q0 = qt * 16 * NQ;
+  const int64_t row0 = (int64_t)(b * a.n_units + lu) * a.U;
+  f32x4 q[NQ][DC];
+#pragma unroll
+  for (int i = 0; i < NQ; ++i)
+#pragma unroll
+    for (int c = 0; c < DC; ++c)
+      q[i][c] = *reinterpret_cast<const f32x4*>((const float*)a.q + (row0 + min(q0 + 16 * i + lr, a.U - 1)) * ldq +
+                                               n * DH + 16 * c + 4 * lg);
+  f32x4 o[NQ][DC];  // O^T: dims 16 c + 4 g + r of query lr
+  float m_run[NQ], l_run[NQ];
+#pragma unroll
+  for (int i = 0; i < NQ; ++i) {
+    m_run[i] = -INFINITY;
+    l_run[i] = 0.f;
+#pragma unroll
+    for (int c = 0; c < DC; ++c) o[i][c] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  float m_run = -INFINITY, l_run = 0.f;
   const int64_t u_lo = u - a.window + 1 > 0 ? u - a.window + 1 : 0;
-  for (int64_t ku = u_lo; ku <= u; ++ku) {
-    const int slot = (int)(ku % a.S);
-    const int64_t ring = ((int64_t)(b * a.G + g) * a.S + slot);
-    const float* kb = (const float*)a.k_ring + ring * a.U_pad * DH;
-    const float* vb = (const float*)a.vt_ring + ring * DH * a.U_pad;
-    for (int k0 = 0; k0 < a.U; k0 += 64) {
-      __syncthreads();
-      for (int e = tid; e < 64 * DH; e += 64) {
-        const int r = e / DH, d = e % DH;
-        sk[r][d] = kb[(int64_t)(k0 + r) * DH + d];
-        sv[d][r] = vb[(int64_t)d * a.U_pad + k0 + r];
+  const int bpu = (a.U + 15) / 16;  // key blocks of a unit
+  const int nb = (int)(u - u_lo + 1) * bpu;
+  const int64_t ring = (int64_t)(b * a.G + g) * a.S;
+  const float* kring = (const float*)a.k_ring + ring * a.U_pad * DH;
+  const float* vring = (const float*)a.vt_ring + ring * DH * a.U_pad;
+  const int slot0 = (int)(u_lo % a.S);
+  for (int t0 = wave; t0 < nb; t0 += 4 * KB) {
+    f32x4 kf[KB][DC], vf[KB][DC];
+    int nk[KB];  // valid keys of each block (0: past the window)
+#pragma unroll
+    for (int e = 0; e < KB; ++e) {
+      const int t = t0 + 4 * e, tc = t < nb ? t : nb - 1;
+      const int ku = tc / bpu, k0 = 16 * (tc - ku * bpu);
+      const int slot = (slot0 + ku) % a.S;
+      nk[e] = t < nb ? min(16, a.U - k0) : 0;
+      const float* kp = kring + ((int64_t)slot * a.U_pad + k0 + lr) * DH + 4 * lg;
+      const float* vp = vring + ((int64_t)slot * DH + lr) * a.U_pad + k0 + 4 * lg;
+#pragma unroll
+      for (int c = 0; c < DC; ++c) {
+        kf[e][c] = *reinterpret_cast<const f32x4*>(kp + 16 * c);
+        vf[e][c] = *reinterpret_cast<const f32x4*>(vp + (int64_t)16 * c * a.U_pad);
       }
-      __syncthreads();
-      const int nk = min(64, a.U - k0);
-      float mx = m_run;
-      for (int j = 0; j < nk; ++j) {
-        float acc = 0.f;
-        for (int d = 0; d < DH; ++d) acc = fmaf(q[d], sk[j][d], acc);
-        const float sc = acc * a.scale;
-        ss[j][tid] = sc;
-        mx = fmaxf(mx, sc);
-      }
-      const float alpha = expf(m_run - mx);
-      for (int d = 0; d < DH; ++d) o[d] *= alpha;
-      l_run *= alpha;
-      for (int j = 0; j < nk; ++j) {
-        const float p = expf(ss[j][tid] - mx);
-        l_run += p;
-        for (int d = 0; d < DH; ++d) o[d] = fmaf(p, sv[d][j], o[d]);
-      }
-      m_run = mx;
+    }
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) {
+      f32x4 s[KB];
+#pragma unroll
+      for (int e = 0; e < KB; ++e) s[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int c = 0; c < DC; ++c)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int e = 0; e < KB; ++e)
+            s[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[e][c][j], q[i][c][j], s[e], 0, 0, 0);
+      float mx = m_run[i];
+#pragma unroll
+      for (int e = 0; e < KB; ++e)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          s[e][r] = 4 * lg + r < nk[e] ? s[e][r] * a.scale : -INFINITY;
+          mx = fmaxf(mx, s[e][r]);
+        }
+      mx = fmaxf(mx, __shfl_xor(mx, 16));
+      mx = fmaxf(mx, __shfl_xor(mx, 32));
+      // (the first block of a step holds a visible key, so mx is finite)
+      const float alpha = expf(m_run[i] - mx);
+      m_run[i] = mx;
+      float ls = 0.f;
+#pragma unroll
+      for (int e = 0; e < KB; ++e)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          s[e][r] = expf(s[e][r] - mx);
+          ls += s[e][r];
+        }
+      l_run[i] = l_run[i] * alpha + ls;
+#pragma unroll
+      for (int c = 0; c < DC; ++c)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) o[i][c][r] *= alpha;
+#pragma unroll
+      for (int e = 0; e < KB; ++e)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int c = 0; c < DC; ++c)
+            o[i][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[e][c][r], s[e][r], o[i][c], 0, 0, 0);
     }
   }
-  if (qi < a.U) {
-    for (int d = 0; d < DH; ++d) ((float*)a.o)[qrow * ldq + n * DH + d] = o[d] / l_run;
+#pragma unroll
+  for (int i = 0; i < NQ; ++i) {
+    float l = l_run[i] + __shfl_xor(l_run[i], 16);
+    l += __shfl_xor(l, 32);
+    if (lg == 0) {
+      sm[wave][16 * i + lr] = m_run[i];
+      sl[wave][16 * i + lr] = l;
+    }
+#pragma unroll
+    for (int c = 0; c < DC; ++c)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) so[wave][16 * i + lr][16 * c + 4 * lg + r] = o[i][c][r];
+  }
+  __syncthreads();
+  for (int x = tid; x < NQ * 16 * DH; x += 256) {
+    const int r = x / DH, d = x % DH;
+    if (q0 + r >= a.U) continue;
+    // wave 0 always holds keys; a wave without any has m = -inf and weight 0
+    const float m = fmaxf(fmaxf(sm[0][r], sm[1][r]), fmaxf(sm[2][r], sm[3][r]));
+    float num = 0.f, den = 0.f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const float f = expf(sm[w][r] - m);
+      num += f * so[w][r][d];
+      den += f * sl[w][r];
+    }
+    ((float*)a.o)[(row0 + q0 + r) * ldq + n * DH + d] = num / den;
   }
 }
 
@@ -485,17 +568,26 @@ hipError_t attention_mfma(Act16 t, const AttnArgs& a, hipStream_t s) {
   return attn_launch<__hip_bfloat16, 1>(a, s);
 }
 
+template <int DH>
+hipError_t attn_f32_launch(const AttnArgs& a, hipStream_t s) {
+  // 32 queries per workgroup read half the K and V bytes per query; 16 where 32
+  // would leave CUs idle
+  const int q16 = (a.U + 15) / 16, q32 = (a.U + 31) / 32;
+  if ((int64_t)q32 * a.n_units * a.B * a.N >= 512)
+    hipLaunchKernelGGL((attn_f32_kernel<DH, 2>), dim3(q32 * a.n_units * a.B, a.N), dim3(256), 0, s, a, q32);
+  else
+    hipLaunchKernelGGL((attn_f32_kernel<DH, 1>), dim3(q16 * a.n_units * a.B, a.N), dim3(256), 0, s, a, q16);
+  return hipGetLastError();
+}
+
 hipError_t attention_f32(const AttnArgs& a, hipStream_t s) {
   if (a.U <= 0 || a.U_pad % 64 || a.N % a.G || a.o_packed) return hipErrorInvalidValue;
-  const int q_tiles = (a.U + 63) / 64;
-  dim3 grid(q_tiles * a.n_units * a.B, a.N);
   switch (a.Dh) {
-    case 16: hipLaunchKernelGGL(attn_f32_kernel<16>, grid, dim3(64), 0, s, a, q_tiles); break;
-    case 32: hipLaunchKernelGGL(attn_f32_kernel<32>, grid, dim3(64), 0, s, a, q_tiles); break;
-    case 64: hipLaunchKernelGGL(attn_f32_kernel<64>, grid, dim3(64), 0, s, a, q_tiles); break;
+    case 16: return attn_f32_launch<16>(a, s);
+    case 32: return attn_f32_launch<32>(a, s);
+    case 64: return attn_f32_launch<64>(a, s);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 }  // namespace fd

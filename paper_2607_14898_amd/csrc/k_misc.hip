@@ -7,7 +7,6 @@
 //                    (unit mod S);
 //  * unshuffle_latent PixelUnshuffle(p) + raster flatten of latent frames
 //                    (Sec. 4.3 and Eq. projection);
-//  * swiglu_f32      SwiGLU gate of the fp32 path;
 //  * quant_rows_e4m3 per-row E4M3 codes and scales of the FP8 MLP (Sec. 4.6).
 #include "fd_kernels.h"
 
@@ -327,17 +326,6 @@ __global__ __launch_bounds__(256) void unshuffle_kernel(const void* z, int z_kin
   }
 }
 
-__global__ __launch_bounds__(256) void swiglu_f32_kernel(const float* raw, int M, int H, float* h) {
-  const int64_t total = (int64_t)M * H;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t m = e / H;
-    const int j = (int)(e % H);
-    const float gt = raw[m * 2 * H + j], up = raw[m * 2 * H + H + j];
-    h[e] = gt / (1.f + expf(-gt)) * up;
-  }
-}
-
 __global__ __launch_bounds__(256) void convert_kernel(const float* src, void* dst, int64_t n,
                                                       int out_kind) {
   for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n;
@@ -410,11 +398,6 @@ hipError_t unshuffle_latent(const void* z, int z_kind, int B, int C, int F, int 
   const int64_t total = (int64_t)B * F * (H / p) * (W / p) * K_pad;
   hipLaunchKernelGGL(unshuffle_kernel, dim3(grid_for(total)), dim3(256), 0, s, z, z_kind, B, C, F,
                      H, W, p, K_pad, u, out_kind, packed ? 1 : 0);
-  return hipGetLastError();
-}
-
-hipError_t swiglu_f32(const float* raw, int M, int H, float* h, hipStream_t s) {
-  hipLaunchKernelGGL(swiglu_f32_kernel, dim3(grid_for((int64_t)M * H)), dim3(256), 0, s, raw, M, H, h);
   return hipGetLastError();
 }
 
