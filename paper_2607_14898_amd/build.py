@@ -12,7 +12,9 @@ from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
-SOURCES = ["csrc/k_gemm.hip", "csrc/k_attn.hip", "csrc/k_misc.hip", "csrc/k_probe.hip", "csrc/fd_scratch.hip",
+SOURCES = ["csrc/k_gemm_f16.hip", "csrc/k_gemm_bf16.hip", "csrc/k_gemm_fp8.hip",
+           "csrc/k_gemm_f32.hip", "csrc/k_gemm.hip",
+           "csrc/k_attn.hip", "csrc/k_misc.hip", "csrc/k_probe.hip", "csrc/fd_scratch.hip",
            "csrc/fd_runtime.cpp"]
 LIB = os.path.join(PKG, "libflashdecoder.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -55,7 +57,7 @@ def _compile(src: str, obj: str) -> None:
         sys.stderr.write(err + "\n")
 
 
-def build(jobs: int = 4) -> str:
+def build(jobs: int = 8) -> str:
     bdir = os.path.join(ROOT, "_build")
     os.makedirs(bdir, exist_ok=True)
     objs = [os.path.join(bdir, os.path.basename(s) + ".o") for s in SOURCES]

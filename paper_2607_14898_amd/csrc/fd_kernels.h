@@ -34,9 +34,8 @@ struct QkvPostArgs {
   const float* knorm_g = nullptr;  // [D_h] or null
   const float* vnorm_g = nullptr;
   const int* rope_axis = nullptr;  // [D_h / 2] axis of each pair (0 t, 1 h, 2 w)
-  const double* rope_freq = nullptr;// [D_h / 2] angular frequency of each pair
   const float2* rope_hw = nullptr;  // [max(grid_h, grid_w)][D_h / 2] (cos, sin) of spatial pairs
-  float2* rope_t = nullptr;         // [(sub-)frames of the call][D_h / 2] temporal (cos, sin), filled here
+  const float2* rope_t = nullptr;   // [(sub-)frames of the call][D_h / 2] temporal (cos, sin)
   int rope = 1;
   float eps = 1e-6f;
   int B = 1, N = 1, G = 1, Dh = 64;
@@ -45,7 +44,6 @@ struct QkvPostArgs {
   int grid_w = 1;
   int U = 0, U_pad = 0, S = 1; // unit geometry of the ring
   int64_t u0 = 0;              // absolute index of the first unit of the call
-  int64_t tau0 = 0;            // temporal position of the call's first (sub-)frame
   int out_kind = 0;            // 0 f16, 1 bf16, 2 fp32
 };
 
@@ -123,6 +121,9 @@ inline int64_t pack_a8_index(int64_t row, int64_t k, int64_t K) { return pack_w8
 // 16-bit operand GEMM on MFMA (K > 0, K % 32 == 0, lda % 8 == 0, 16-byte aligned
 // A, row-major or packed; W packed as above).
 hipError_t gemm_mfma(Act16 t, const GemmArgs& g, hipStream_t stream);
+// (its two operand types, arguments already checked)
+hipError_t gemm_mfma_f16(const GemmArgs& g, hipStream_t stream);
+hipError_t gemm_mfma_bf16(const GemmArgs& g, hipStream_t stream);
 // fp32 GEMM (any shape) for the fp32 compute path. EPI_SWIGLU: W rows are gate
 // rows 0 .. N/2 - 1, then up rows (not interleaved); out_a is fp32.
 hipError_t gemm_f32(const GemmArgs& g, hipStream_t stream);
@@ -175,14 +176,22 @@ hipError_t quant_rows_e4m3(const void* in, int in_kind, int64_t M, int K, uint8_
 // Split raw qkv (fp32, bias included) into rotated queries and the KV ring
 // (KV-norm, RoPE) for rows of one call.
 hipError_t qkv_post(const QkvPostArgs& a, hipStream_t stream);
-// Temporal (cos, sin) of the call's (sub-)frames into a.rope_t; run once per
-// stack and call, before the QKV post step of its layers.
-hipError_t rope_time(const QkvPostArgs& a, hipStream_t stream);
-
-// PixelUnshuffle + flatten of latent frames into embedding operands [B F L, K_pad]
-// (packed: 16-bit output in the packed operand layout, K = K_pad).
-hipError_t unshuffle_latent(const void* z, int z_kind, int B, int C, int F, int H, int W, int p,
-                            int K_pad, void* u, int out_kind, hipStream_t stream, bool packed = false);
+// Temporal (cos, sin) of a stack's (sub-)frames: n_fs entries of D_h / 2 pairs
+// for positions tau0 .., into out (n_fs 0: none).
+struct RopeTimeArgs {
+  int64_t tau0 = 0;
+  int n_fs = 0;
+  const int* axis = nullptr;      // [D_h / 2]
+  const double* freq = nullptr;   // [D_h / 2]
+  float2* out = nullptr;
+};
+// What a call starts with, in one launch: PixelUnshuffle + flatten of latent
+// frames into embedding operands [B F L, K_pad] (packed: 16-bit output in the
+// packed operand layout, K = K_pad), and the temporal RoPE tables of both
+// stacks (np = D_h / 2).
+hipError_t prologue(const void* z, int z_kind, int B, int C, int F, int H, int W, int p, int K_pad, void* u,
+                    int out_kind, bool packed, const RopeTimeArgs& r0, const RopeTimeArgs& r1, int np,
+                    hipStream_t stream);
 
 // Sustained MFMA throughput probe: `blocks` workgroups of 4 waves issue 16
 // 32x32x16 MFMAs per iteration each; clk receives per workgroup the shader

@@ -443,7 +443,7 @@ fd_status trace_copy(Ctx& x, const float* src, int64_t n) {
 
 // One transformer stack (backbone or refinement) over the rows of this call.
 fd_status run_stack(Ctx& x, const std::vector<LayerW>& layers, float* xs, int rows_per_batch,
-                    int U, int U_pad, int64_t tau0, const std::vector<void*>& kr,
+                    int U, int U_pad, const float2* rope_t, const std::vector<void*>& kr,
                     const std::vector<void*>& vr, bool refine) {
   const int layer0 = refine ? x.dec->cfg.n_backbone_blocks : 0;  // index of the FP8 scales
   const fd_decoder* dec = x.dec;
@@ -460,9 +460,8 @@ fd_status run_stack(Ctx& x, const std::vector<LayerW>& layers, float* xs, int ro
   qa.raw = kc->raw;
   qa.q = kc->q;
   qa.rope_axis = dec->rope_axis;
-  qa.rope_freq = dec->rope_freq;
   qa.rope_hw = dec->rope_hw;
-  qa.rope_t = kc->rope_t;
+  qa.rope_t = rope_t;
   qa.rope = c.rope;
   qa.eps = c.norm_eps;
   qa.B = B;
@@ -476,11 +475,8 @@ fd_status run_stack(Ctx& x, const std::vector<LayerW>& layers, float* xs, int ro
   qa.U_pad = U_pad;
   qa.S = kc->S;
   qa.u0 = u0;
-  qa.tau0 = tau0;
   qa.out_kind = d.act_kind;
-  // temporal RoPE angles of this call's (sub-)frames, once for the whole stack
-  hipError_t e = fd::rope_time(qa, x.s);
-  if (e != hipSuccess) return fail(FD_ERR_DEVICE, "rope_time launch failed: %s", hipGetErrorString(e));
+  hipError_t e;
   for (size_t l = 0; l < layers.size(); ++l) {
     const LayerW& w = layers[l];
     fd_status st = run_norm(x, xs, rows, w.n1g, w.n1b);
@@ -654,10 +650,26 @@ fd_status decode(const fd_decoder* dec, const void* latent, int32_t latent_dtype
   hipEvent_t ev;
   do {
     if ((st = probe_begin(kc, FD_KC_EMBED_IN, s, &ev))) break;
-    hipError_t e = fd::unshuffle_latent(latent, latent_dtype == FD_DTYPE_F32 ? 0 : (latent_dtype == FD_DTYPE_BF16 ? 1 : 2),
-                                        B, c.latent_channels, F, c.latent_h, c.latent_w, c.patch,
-                                        d.K_pad, kc->u, d.act_kind, s, d.is16);
-    if (e != hipSuccess) { st = fail(FD_ERR_DEVICE, "unshuffle launch failed: %s", hipGetErrorString(e)); break; }
+    // temporal RoPE tables: the backbone's sits in the refinement stream's buffer
+    // (which the temporal upsampling fills after the backbone's last use of it),
+    // the refinement's in rope_t; without a refinement stack the backbone's does
+    const bool tf = c.head_kind == FD_HEAD_TEMPORAL_FIRST;
+    float2* rt_bb = tf ? (float2*)kc->x_rf : kc->rope_t;
+    fd::RopeTimeArgs r0, r1;
+    r0.axis = r1.axis = dec->rope_axis;
+    r0.freq = r1.freq = dec->rope_freq;
+    if (c.rope) {
+      r0.tau0 = kc->t;
+      r0.n_fs = F;
+      r0.out = rt_bb;
+      r1.tau0 = kc->t * c.r_t;
+      r1.n_fs = tf ? F * c.r_t : 0;
+      r1.out = kc->rope_t;
+    }
+    hipError_t e = fd::prologue(latent, latent_dtype == FD_DTYPE_F32 ? 0 : (latent_dtype == FD_DTYPE_BF16 ? 1 : 2),
+                                B, c.latent_channels, F, c.latent_h, c.latent_w, c.patch, d.K_pad, kc->u, d.act_kind,
+                                d.is16, r0, r1, d.Dh / 2, s);
+    if (e != hipSuccess) { st = fail(FD_ERR_DEVICE, "prologue launch failed: %s", hipGetErrorString(e)); break; }
     if ((st = probe_end(kc, s, ev, (double)M * d.K_in * (latent_dtype == FD_DTYPE_F32 ? 4 : 2) +
                                        (double)M * d.K_pad * d.act_bytes))) break;
     fd::GemmArgs g = gemm_args(kc->u, d.K_pad, dec->embed_w, M, D, d.K_pad, fd::EPI_STORE_F32, dec->embed_b);
@@ -665,7 +677,7 @@ fd_status decode(const fd_decoder* dec, const void* latent, int32_t latent_dtype
     g.ep.ld_out = D;
     if ((st = run_gemm(x, g, d.K_in))) break;
     if ((st = trace_copy(x, kc->x_bb, (int64_t)M * D))) break;
-    if ((st = run_stack(x, dec->bb, kc->x_bb, F * d.L, c.unit_frames * d.L, kc->U_bb_pad, kc->t,
+    if ((st = run_stack(x, dec->bb, kc->x_bb, F * d.L, c.unit_frames * d.L, kc->U_bb_pad, rt_bb,
                         kc->k_bb, kc->v_bb, false))) break;
     if ((st = run_norm(x, kc->x_bb, M, dec->bbf_g, dec->bbf_b))) break;
     if (c.head_kind == FD_HEAD_TEMPORAL_FIRST) {
@@ -679,7 +691,7 @@ fd_status decode(const fd_decoder* dec, const void* latent, int32_t latent_dtype
       if ((st = run_gemm(x, g, D))) break;
       if ((st = trace_copy(x, kc->x_rf, (int64_t)MR * D))) break;
       if ((st = run_stack(x, dec->rf, kc->x_rf, F * c.r_t * d.L, c.unit_frames * c.r_t * d.L,
-                          kc->U_rf_pad, kc->t * c.r_t, kc->k_rf, kc->v_rf, true))) break;
+                          kc->U_rf_pad, kc->rope_t, kc->k_rf, kc->v_rf, true))) break;
       if ((st = run_norm(x, kc->x_rf, MR, dec->rff_g, dec->rff_b))) break;
       g = gemm_args(kc->a, D, dec->head1_w, MR, c.head_hidden, D, fd::EPI_STORE_SILU, dec->head1_b);
       g.ep.sat = kc->sat;

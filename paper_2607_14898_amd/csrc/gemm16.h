@@ -1,0 +1,288 @@
+// Dense projections of the decoder: C = A W^T + b with fused epilogues.
+//
+// Every Linear layer of the decoder goes through here: the latent projection
+// (Eq. projection), the QKV / output / MLP projections of each block (Sec. 3.2),
+// the temporal upsampling Linear D -> r_t D (Eq. temporal_upsample) and the
+// 2-layer pixel head (Sec. 3.4 Step 3). The epilogues fuse what follows each
+// projection: bias, residual add into the fp32 stream, SiLU / GELU / SwiGLU,
+// the channel -> sub-frame reshape of Step 1 and the PixelShuffle store.
+//
+// 16-bit path: one workgroup of wave64s computes a BM x BN tile with the
+// gfx950 32x32x16 MFMA (fp32 accumulate). A and W are both K-contiguous; K
+// tiles of 32 columns are copied from memory straight into LDS by the buffer
+// unit (buffer_load ... lds, no register staging) several tiles ahead of the
+// MFMAs, and read back as MFMA fragments with 16-byte ds_read_b128 per lane
+// through a per-row XOR swizzle of the 16-byte chunks that keeps the 16 rows
+// one ds_read_b128 serves at once in 16 different bank groups.
+#pragma once
+
+#include "gemm_tile.h"
+
+namespace fd {
+namespace {
+
+template <typename T, class C, int EPI>
+__global__ __launch_bounds__(C::NT, C::MIN_BLOCKS) void gemm_mfma_kernel(
+    const T* __restrict__ A, const T* __restrict__ W, int M, int N, int K, int lda, int ldw,
+    EpiParams ep, int tiles_m, int tiles_n, int vec_store, int a_packed) {
+  constexpr int BM = C::BM, BN = C::BN, FM = C::FM, FN = C::FN, NS = C::NS, NW = C::NW;
+  constexpr int QA = C::QA, Q = C::QA + C::QB, STAGE = C::STAGE;
+  using V = typename Mfma<T>::V;
+  __shared__ uint4 lds[NS * STAGE];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int tm, tn;
+  tile_of(blockIdx.x, tiles_m * tiles_n, tiles_m, tiles_n, tm, tn);
+  const int m0 = tm * BM, n0 = tn * BN;
+  const int wm0 = (wave / C::WAVES_N) * C::WM, wn0 = (wave % C::WAVES_N) * C::WN;
+
+  // W is packed K-tile-major: blocks of 16 rows x 32 K-columns (1 KB), block
+  // (row / 16, k / 32) at ((row / 16) (K / 32) + k / 32) KB, rows padded with
+  // zeros to a multiple of 16, so each DMA of W reads one contiguous 1 KB
+  // block. A is row-major (lda), or packed the same way (lda = K, whole
+  // 16-row blocks readable).
+  const int KB = K / BKD;  // K tiles
+  const bool apk = a_packed != 0;
+  const int a_rows = apk ? (min(BM, M - m0) + 15) / 16 * 16 : min(BM, M - m0);
+  const __amdgpu_buffer_rsrc_t rA =
+      make_rsrc(A + (int64_t)m0 * lda, (uint32_t)a_rows * lda * (uint32_t)sizeof(T));
+  const uint32_t a_kstep = apk ? 1024u : (uint32_t)BKD * (uint32_t)sizeof(T);  // bytes per K tile
+  const int nrows_w = min(BN, (N + 15) / 16 * 16 - n0);
+  const __amdgpu_buffer_rsrc_t rB =
+      make_rsrc(W + (int64_t)(n0 / 16) * KB * 512, (uint32_t)(nrows_w / 16) * KB * 1024u);
+  (void)ldw;
+  // DMA j of this wave fills stage rows 16 q .. 16 q + 15, q = j NW + wave (A
+  // rows for j < QA, W rows after); lane l lands in row 16 q + l / 4, physical
+  // chunk l % 4, which holds K-chunk (l % 4) ^ ((l / 16) % 4).
+  const int lrow = lane >> 2, lchunk = (lane & 3) ^ ((lane >> 4) & 3);
+  uint32_t voff[Q];
+#pragma unroll
+  for (int j = 0; j < Q; ++j) {
+    const int q = j * NW + wave;
+    voff[j] = j >= QA ? (uint32_t)(q - BM / 16) * KB * 1024u + (uint32_t)(lrow * 64 + lchunk * 16)
+              : apk   ? (uint32_t)q * KB * 1024u + (uint32_t)(lrow * 64 + lchunk * 16)
+                      : (uint32_t)((16 * q + lrow) * lda + lchunk * 8) * (uint32_t)sizeof(T);
+  }
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint4*)lds;
+  // DMA instruction j of the refill of stage st with K tile kt
+  auto dma1 = [&](int st, int kt, int j) {
+    const uint32_t soff = j < QA ? (uint32_t)kt * a_kstep : (uint32_t)kt * 1024u;
+    const uint32_t m0addr = lds0 + (uint32_t)(st * STAGE + 64 * (j * NW + wave)) * 16u;
+    // M0 is reserved by the compiler, but nothing else in this kernel reads it
+    // (no LDS DMA builtins, interpolation, GWS or message sends).
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :
+                 : "s"(m0addr), "v"(voff[j]), "s"(j < QA ? rA : rB), "s"(soff)
+                 : "m0");
+#pragma clang diagnostic pop
+  };
+  auto dma = [&](int st, int kt) {
+#pragma unroll
+    for (int j = 0; j < Q; ++j) dma1(st, kt, j);
+  };
+  // Every wave waits for its own DMAs of the next tile (all but the (NS - 2) Q
+  // youngest, or all of them near the end of K) and for its LDS reads; the
+  // barrier then makes the tile visible and frees the stage read before it.
+  auto sync = [&](bool drain) {
+    if (drain) __builtin_amdgcn_s_waitcnt(FD_VMCNT(0));
+    else __builtin_amdgcn_s_waitcnt(FD_VMCNT((NS - 2) * Q));
+    __builtin_amdgcn_s_waitcnt(FD_LGKMCNT0);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+
+  f32x16 acc[FM][FN];
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+  const int lr = lane & 31, lk = lane >> 5, xr = (lr >> 2) & 3;
+  // slot of fragment row (A: wm0 + lr, W: BM + wn0 + lr) at k-step ks: K-chunk 2 ks + lk
+  const int ia0 = (wm0 + lr) * 4 + (lk ^ xr), ia1 = (wm0 + lr) * 4 + ((2 + lk) ^ xr);
+  const int ib0 = (BM + wn0 + lr) * 4 + (lk ^ xr), ib1 = (BM + wn0 + lr) * 4 + ((2 + lk) ^ xr);
+  V fa[2][FM], fb[2][FN];
+  auto load_frags = [&](int slot, int st, int ks) {
+    const uint4* sb = lds + st * STAGE;
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+      const uint4 v = sb[(ks ? ia1 : ia0) + i * 128];
+      fa[slot][i] = *reinterpret_cast<const V*>(&v);
+    }
+#pragma unroll
+    for (int j = 0; j < FN; ++j) {
+      const uint4 v = sb[(ks ? ib1 : ib0) + j * 128];
+      fb[slot][j] = *reinterpret_cast<const V*>(&v);
+    }
+  };
+  auto mfmas = [&](int slot) {
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+        acc[i][j] = kTransposed<EPI> ? Mfma<T>::run(fb[slot][j], fa[slot][i], acc[i][j])
+                                     : Mfma<T>::run(fa[slot][i], fb[slot][j], acc[i][j]);
+  };
+  // the MFMAs of a k-step with DMA instructions j0 .. j0 + Q / 2 - 1 of a
+  // stage refill between them, evenly spaced, in this order
+  auto mfmas_dma = [&](int slot, int st, int kt, int j0) {
+    if constexpr (C::IL) {
+      constexpr int NM = FM * FN, ND = Q / 2, EVERY = NM / ND;
+      static_assert(Q % 2 == 0 && NM % ND == 0, "DMA spacing");
+#pragma unroll
+      for (int m = 0; m < NM; ++m) {
+        const int i = m / FN, j = m % FN;
+        acc[i][j] = kTransposed<EPI> ? Mfma<T>::run(fb[slot][j], fa[slot][i], acc[i][j])
+                                     : Mfma<T>::run(fa[slot][i], fb[slot][j], acc[i][j]);
+        if (m % EVERY == EVERY - 1) {
+          __builtin_amdgcn_sched_barrier(0);
+          dma1(st, kt, j0 + m / EVERY);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    }
+  };
+
+  // Tile t sits in stage t % NS. The loop starts at the barrier (whose
+  // explicit lgkmcnt(0) leaves no LDS read pending at the loop header), then
+  // reads k-step 0 of tile t + 1, multiplies k-step 1 of tile t, reads k-step 1
+  // of tile t + 1, refills the stage of tile t (read by everyone before the
+  // barrier) with tile t + NS, and multiplies k-step 0 of tile t + 1.
+  const int KT = K / BKD;
+#pragma unroll
+  for (int p = 0; p < NS - 1; ++p)
+    if (p < KT) dma(p, p);
+  sync(KT < NS - 1);
+  load_frags(0, 0, 0);
+  load_frags(1, 0, 1);
+  if (NS - 1 < KT) dma(NS - 1, NS - 1);
+  mfmas(0);
+  int sc = 0;  // stage of tile t
+  int t = 0;
+  if constexpr (C::IL) {
+    for (; t < KT - NS; ++t) {
+      const int sn = sc + 1 == NS ? 0 : sc + 1;
+      sync(false);
+      load_frags(0, sn, 0);
+      mfmas_dma(1, sc, t + NS, 0);
+      load_frags(1, sn, 1);
+      mfmas_dma(0, sc, t + NS, Q / 2);
+      sc = sn;
+    }
+  }
+  for (; t < KT - 1; ++t) {
+    const int sn = sc + 1 == NS ? 0 : sc + 1;
+    sync(t + NS - 1 >= KT);
+    load_frags(0, sn, 0);
+    mfmas(1);
+    load_frags(1, sn, 1);
+    if (t + NS < KT) dma(sc, t + NS);
+    mfmas(0);
+    sc = sn;
+  }
+  mfmas(1);
+  static_assert(EPI != EPI_QKV || NW * 32 * 68 * 4 <= NS * STAGE * 16, "QKV epilogue staging fits the stage buffers");
+  if constexpr (kTransposed<EPI>)
+    store_tile_t<EPI, T, FM, FN>(ep, acc, m0 + wm0, n0 + wn0, M, N, lr, lk, vec_store != 0);
+  else if constexpr (EPI == EPI_PIXEL || EPI == EPI_LINEAR_PIXEL) {
+    // one instantiation per pixel format, chosen once per tile (a format test
+    // per store makes the epilogue loops too large to unroll, and the
+    // accumulators would go to scratch memory)
+    constexpr bool R = !(C::NW == 4 && C::MIN_BLOCKS == 1);
+    float* ws = reinterpret_cast<float*>(lds);
+    if (ep.out_fmt == 0) store_tile<EPI, T, FM, FN, R, 0>(ep, acc, m0 + wm0, n0 + wn0, M, N, lr, lk, ws);
+    else if (ep.out_fmt == 1) store_tile<EPI, T, FM, FN, R, 1>(ep, acc, m0 + wm0, n0 + wn0, M, N, lr, lk, ws);
+    else store_tile<EPI, T, FM, FN, R, 2>(ep, acc, m0 + wm0, n0 + wn0, M, N, lr, lk, ws);
+  } else {
+    store_tile<EPI, T, FM, FN, !(C::NW == 4 && C::MIN_BLOCKS == 1)>(ep, acc, m0 + wm0, n0 + wn0, M, N, lr, lk,
+                                                                   reinterpret_cast<float*>(lds));
+  }
+}
+
+template <typename T, class C, int EPI>
+hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
+  const int tm = (g.M + C::BM - 1) / C::BM, tn = (g.N + C::BN - 1) / C::BN;
+  // four consecutive output columns land contiguously and 16-byte aligned
+  // (fp32) / 8-byte aligned (16-bit) in the destination
+  bool vec = g.N % 4 == 0 && g.ep.ld_out % 4 == 0;
+  if (EPI == EPI_PIXEL || EPI == EPI_LINEAR_PIXEL) vec = vec && g.ep.s % 4 == 0;
+  if (EPI == EPI_TUP) vec = vec && g.ep.dim % 4 == 0;
+  vec = vec && ((uintptr_t)g.ep.out_f % 16 == 0) && ((uintptr_t)g.ep.out_a % 8 == 0);
+  hipLaunchKernelGGL((gemm_mfma_kernel<T, C, EPI>), dim3(tm * tn), dim3(C::NT), 0, s,
+                     (const T*)g.A, (const T*)g.W, g.M, g.N, g.K, g.lda, g.ldw, g.ep, tm, tn, vec ? 1 : 0,
+                     g.a_packed);
+  return hipGetLastError();
+}
+
+// Tile choice, measured on the 480p / 720p decoder shapes (random fp16 data).
+// - 256 x 256 tiles (8 waves of 128 x 64) read the fewest LDS and L2 bytes
+//   per flop and win wherever there are enough of them to fill the 256 CUs,
+//   except for residual-add epilogues behind a short K loop.
+// - When 192 x 128 tiles come to one nearly full wave (200-256 workgroups,
+//   the backbone's M = 3600 x N = 1536 projections), one workgroup per CU with
+//   6 stages in flight wins.
+// - When even 128 x 128 tiles leave CUs idle (480p backbone), each CU runs a
+//   single workgroup, so it gets 6 stages in flight.
+// - Otherwise 128 x 128 tiles with 3 stages, several workgroups per CU, so one
+//   workgroup's epilogue and barriers overlap another's MFMAs.
+template <typename T, int EPI>
+hipError_t dispatch_tiles(const GemmArgs& g, hipStream_t s) {
+  auto tiles = [&](int bm, int bn) { return ((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn); };
+  const bool short_rmw = EPI == EPI_RESID_ADD && g.K <= 2048;
+  if (tiles(256, 256) >= 160 && !short_rmw) {
+    // a SwiGLU projection of under two rounds of 256 x 256 tiles (the 480p
+    // backbone: 336 tiles, 1.3 rounds) runs faster as 128 x 128 tiles, several
+    // per CU (measured 1.8% per 480p chunk); so do the QKV and temporal-up
+    // projections of the 720p refinement input (456 and 360 tiles)
+    if (EPI == EPI_SWIGLU && tiles(256, 256) < 512) return launch_gemm<T, TileS, EPI>(g, s);
+    if ((EPI == EPI_QKV || EPI == EPI_TUP) && tiles(256, 256) < 512) return launch_gemm<T, TileS, EPI>(g, s);
+    // 256 x 192 tiles where their rounds of 256 CUs, weighted by tile area,
+    // are fewer than those of 256 x 256 tiles (for instance 342 -> 456 tiles,
+    // 2 -> 1.5 round-equivalents, for 14400 x 1536 outputs). Their 96-column
+    // wave blocks suit every epilogue but the paired SwiGLU and the QKV post
+    // step (one 64-column head vector per wave); the GELU epilogue's erf needs
+    // more registers than a 4-wave 256 x 192 tile leaves.
+    if constexpr (EPI != EPI_SWIGLU && EPI != EPI_QKV && EPI != EPI_STORE_GELU) {
+      const int rounds_l = (tiles(256, 256) + 255) / 256, rounds_w = (tiles(256, 192) + 255) / 256;
+      if (4 * rounds_w * 3 < 4 * rounds_l * 4) return launch_gemm<T, TileW, EPI>(g, s);
+    }
+    return launch_gemm<T, TileL, EPI>(g, s);
+  }
+  const int tm = tiles(192, 128);
+  if constexpr (EPI == EPI_RESID_ADD) {
+    // residual adds: 192 x 128 tiles with 4 stages (two workgroups per CU)
+    // behind a long K loop in one round, and wherever 192 x 128 tiles make one
+    // round of two per CU (257-512 tiles, the 480p refinement O projection)
+    if ((tm >= 200 && tm <= 256 && g.K > 2048) || (tm > 256 && tm <= 512))
+      return launch_gemm<T, TileM4, EPI>(g, s);
+  }
+  if (tm >= 200 && tm <= 256) return launch_gemm<T, TileM, EPI>(g, s);
+  if (tiles(128, 128) <= 256) return launch_gemm<T, TileS1, EPI>(g, s);
+  return launch_gemm<T, TileS, EPI>(g, s);
+}
+
+template <typename T>
+hipError_t dispatch_epi(const GemmArgs& g, hipStream_t s) {
+  switch (g.epi) {
+    case EPI_STORE_F32: return dispatch_tiles<T, EPI_STORE_F32>(g, s);
+    case EPI_RESID_ADD: return dispatch_tiles<T, EPI_RESID_ADD>(g, s);
+    case EPI_STORE_ACT: return dispatch_tiles<T, EPI_STORE_ACT>(g, s);
+    case EPI_STORE_SILU: return dispatch_tiles<T, EPI_STORE_SILU>(g, s);
+    case EPI_STORE_GELU: return dispatch_tiles<T, EPI_STORE_GELU>(g, s);
+    case EPI_SWIGLU: return dispatch_tiles<T, EPI_SWIGLU>(g, s);
+    case EPI_TUP: return dispatch_tiles<T, EPI_TUP>(g, s);
+    case EPI_PIXEL: return dispatch_tiles<T, EPI_PIXEL>(g, s);
+    case EPI_LINEAR_PIXEL: return dispatch_tiles<T, EPI_LINEAR_PIXEL>(g, s);
+    case EPI_QKV: return dispatch_tiles<T, EPI_QKV>(g, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+}  // namespace
+}  // namespace fd

@@ -5,12 +5,15 @@
 //  * qkv_post        KV-norm and 3D-RoPE (Sec. 3.2), then the rolling-cache
 //                    append of Sec. 3.3 / Algorithm 1 as a write into ring slot
 //                    (unit mod S);
-//  * unshuffle_latent PixelUnshuffle(p) + raster flatten of latent frames
-//                    (Sec. 4.3 and Eq. projection);
+//  * prologue        PixelUnshuffle(p) + raster flatten of latent frames
+//                    (Sec. 4.3 and Eq. projection) and the call's temporal
+//                    RoPE tables;
 //  * quant_rows_e4m3 per-row E4M3 codes and scales of the FP8 MLP (Sec. 4.6).
 #include "fd_kernels.h"
 
 #include <hip/hip_bf16.h>
+
+#include <type_traits>
 
 namespace fd {
 namespace {
@@ -81,12 +84,16 @@ struct E4m3Row {
   }
 };
 
-// One wave per row; rows of D floats (D % 4 == 0).
-template <int KIND>
+// One wave per row; rows of D floats (D % 4 == 0), NV = ceil(D / 256) float4 per
+// lane, all valid when FULL (D % 256 == 0; NV = 8 and FULL = false take any D up
+// to 2048). A row is one chain of load, wave reduction, store, so what a small
+// pass costs is latency: the row and gain loads go out together, unbranched
+// (60 rows of 1536: 6.6 -> 3.8 us).
+template <int KIND, int OUT, int NV, bool FULL>
 __global__ __launch_bounds__(256) void norm_kernel(const float* __restrict__ x, int M, int D,
                                                    const float* __restrict__ g,
                                                    const float* __restrict__ bta, float eps,
-                                                   void* out, int out_kind, float* row_scale,
+                                                   void* out, float* row_scale,
                                                    const float* __restrict__ static_sc,
                                                    unsigned* __restrict__ amax_out, int packed) {
   const int lane = threadIdx.x & 63;
@@ -94,17 +101,20 @@ __global__ __launch_bounds__(256) void norm_kernel(const float* __restrict__ x, 
   if (row >= M) return;
   const float4* xr = reinterpret_cast<const float4*>(x + (int64_t)row * D);
   const int nv = D / 4;
-  constexpr int MAXV = 8;  // up to D = 2048 held in registers
-  float4 v[MAXV];
+  float4 v[NV], gv[NV], bv[KIND == 1 ? NV : 1];
   float s = 0.f;
 #pragma unroll
-  for (int i = 0; i < MAXV; ++i) {
-    const int c = lane + 64 * i;
-    if (c < nv) {
-      v[i] = xr[c];
-      s += KIND == 0 ? v[i].x * v[i].x + v[i].y * v[i].y + v[i].z * v[i].z + v[i].w * v[i].w
-                     : v[i].x + v[i].y + v[i].z + v[i].w;
-    }
+  for (int i = 0; i < NV; ++i) {
+    const int c = FULL ? lane + 64 * i : min(lane + 64 * i, nv - 1);
+    v[i] = xr[c];
+    gv[i] = reinterpret_cast<const float4*>(g)[c];
+    if (KIND == 1) bv[i] = reinterpret_cast<const float4*>(bta)[c];
+  }
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const float t = KIND == 0 ? v[i].x * v[i].x + v[i].y * v[i].y + v[i].z * v[i].z + v[i].w * v[i].w
+                              : v[i].x + v[i].y + v[i].z + v[i].w;
+    if (FULL || lane + 64 * i < nv) s += t;
   }
   s = wave_sum(s);
   float mu = 0.f, rs;
@@ -114,44 +124,39 @@ __global__ __launch_bounds__(256) void norm_kernel(const float* __restrict__ x, 
     mu = s / D;
     float q = 0.f;
 #pragma unroll
-    for (int i = 0; i < MAXV; ++i) {
-      const int c = lane + 64 * i;
-      if (c < nv) {
-        const float a0 = v[i].x - mu, a1 = v[i].y - mu, a2 = v[i].z - mu, a3 = v[i].w - mu;
-        q += a0 * a0 + a1 * a1 + a2 * a2 + a3 * a3;
-      }
+    for (int i = 0; i < NV; ++i) {
+      const float a0 = v[i].x - mu, a1 = v[i].y - mu, a2 = v[i].z - mu, a3 = v[i].w - mu;
+      if (FULL || lane + 64 * i < nv) q += a0 * a0 + a1 * a1 + a2 * a2 + a3 * a3;
     }
     q = wave_sum(q);
     rs = rsqrtf(q / D + eps);
   }
   float amax = 0.f;
 #pragma unroll
-  for (int i = 0; i < MAXV; ++i) {
+  for (int i = 0; i < NV; ++i) {
     const int c = lane + 64 * i;
-    if (c < nv) {
-      const float4 gv = reinterpret_cast<const float4*>(g)[c];
-      float4 y = make_float4((v[i].x - mu) * rs * gv.x, (v[i].y - mu) * rs * gv.y,
-                             (v[i].z - mu) * rs * gv.z, (v[i].w - mu) * rs * gv.w);
+    if (FULL || c < nv) {
+      float4 y = make_float4((v[i].x - mu) * rs * gv[i].x, (v[i].y - mu) * rs * gv[i].y,
+                             (v[i].z - mu) * rs * gv[i].z, (v[i].w - mu) * rs * gv[i].w);
       if (KIND == 1) {
-        const float4 bv = reinterpret_cast<const float4*>(bta)[c];
-        y.x += bv.x; y.y += bv.y; y.z += bv.z; y.w += bv.w;
+        y.x += bv[i].x; y.y += bv[i].y; y.z += bv[i].z; y.w += bv[i].w;
       }
-      if (out_kind == 3) {  // E4M3: keep the row for its amplitude
+      if (OUT == 3) {  // E4M3: keep the row for its amplitude
         v[i] = y;
         amax = fmaxf(fmaxf(amax, fmaxf(fabsf(y.x), fabsf(y.y))), fmaxf(fabsf(y.z), fabsf(y.w)));
       } else {
-        store4(out, packed ? pk16(row, 4 * c, D) : (int64_t)row * D + 4 * c, y, out_kind);
+        store4(out, packed ? pk16(row, 4 * c, D) : (int64_t)row * D + 4 * c, y, OUT);
       }
     }
   }
-  if (out_kind == 3) {
+  if (OUT == 3) {
     const float m = wave_max(amax);
     if (amax_out && lane == 0) atomicMax(amax_out, __float_as_uint(m));  // non-negative: ordered as bits
     const E4m3Row q = static_sc ? E4m3Row(static_sc) : E4m3Row(m);
 #pragma unroll
-    for (int i = 0; i < MAXV; ++i) {
+    for (int i = 0; i < NV; ++i) {
       const int c = lane + 64 * i;
-      if (c < nv)
+      if (FULL || c < nv)
         *reinterpret_cast<uint32_t*>((uint8_t*)out + (packed ? pk8(row, 4 * c, D) : (int64_t)row * D + 4 * c)) =
             q.pack4(v[i].x, v[i].y, v[i].z, v[i].w);
     }
@@ -201,30 +206,62 @@ __device__ __forceinline__ float2 rope_cs(const QkvPostArgs& a, int pair, int fs
   return a.rope_hw[p * np + pair];
 }
 
-// Queries and keys: one thread per 4 consecutive channels of a (row, head slot),
-// slots 0..N-1 query heads and N..N+G-1 key groups, so a head vector is 16
-// consecutive lanes (D_h = 64; D_h / 4 lanes in general) and consecutive
-// threads read consecutive 16-byte chunks of the raw projection.
-__global__ __launch_bounds__(256) void qk_post_kernel(QkvPostArgs a, int rows) {
+// The fp32 path's QKV post step in one launch: workgroups below qk_blocks take
+// queries and keys, one thread per 4 consecutive channels of a (row, head slot),
+// slots 0..N-1 query heads and N..N+G-1 key groups, so a head vector is Dh / 4
+// consecutive lanes; the others take values, one workgroup per 64 consecutive
+// positions of one causal unit, one stream and one KV group, KV-normed by the
+// same lane layout and written transposed ([D_h][U_pad] per slot) through LDS.
+// (As two launches, the values with one 64-lane sum per row: 9 + 4 us at 130
+// rows, where a launch's latency is all there is.)
+constexpr int VP_ROWS = 64;
+__global__ __launch_bounds__(256) void qkv_post_kernel(QkvPostArgs a, int rows, int qk_blocks, int blocks_per_unit) {
+  __shared__ float vt[64][VP_ROWS + 1];  // [dim][position]
   const int Dh = a.Dh, qpv = Dh / 4;  // threads per head vector
+  const int width = a.N * Dh + 2 * a.G * Dh;
+  // KV-norm: RMSNorm over D_h (the qpv lanes of the vector) with a learned gain
+  auto kvnorm = [&](float4 x, const float* gain, int qd) {
+    float ss = x.x * x.x + x.y * x.y + x.z * x.z + x.w * x.w;
+    for (int o = qpv / 2; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
+    const float r = rsqrtf(ss / Dh + a.eps);
+    const float4 gv = reinterpret_cast<const float4*>(gain)[qd];
+    return make_float4(x.x * r * gv.x, x.y * r * gv.y, x.z * r * gv.z, x.w * r * gv.w);
+  };
+  if ((int)blockIdx.x >= qk_blocks) {  // values
+    const int vb = blockIdx.x - qk_blocks;
+    const int g = vb % a.G, blk = vb / a.G % blocks_per_unit, bu = vb / a.G / blocks_per_unit;
+    const int units_per_batch = a.rows_per_batch / a.U;
+    const int lu = bu % units_per_batch, b = bu / units_per_batch;
+    const int pos0 = blk * VP_ROWS;
+    const int npos = min(VP_ROWS, a.U - pos0);
+    const int64_t row0 = (int64_t)b * a.rows_per_batch + (int64_t)lu * a.U + pos0;
+    const int per = 256 / qpv, qd = threadIdx.x % qpv;
+    for (int p = threadIdx.x / qpv; p < VP_ROWS; p += per) {
+      float4 x = *reinterpret_cast<const float4*>(a.raw + (row0 + min(p, npos - 1)) * width + (a.N + a.G + g) * Dh + 4 * qd);
+      if (a.vnorm_g) x = kvnorm(x, a.vnorm_g, qd);
+      vt[4 * qd][p] = x.x;
+      vt[4 * qd + 1][p] = x.y;
+      vt[4 * qd + 2][p] = x.z;
+      vt[4 * qd + 3][p] = x.w;
+    }
+    __syncthreads();
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int slot = (int)((a.u0 + lu) % a.S);
+    const int64_t vbase = ((int64_t)(b * a.G + g) * a.S + slot) * Dh * a.U_pad + pos0;
+    for (int d = wave; d < Dh; d += 4)
+      if (lane < npos) store_kind(a.vt_ring, vbase + (int64_t)d * a.U_pad + lane, vt[d][lane], a.out_kind);
+    return;
+  }
   const int slots = a.N + a.G;
   const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int64_t per_row = (int64_t)slots * qpv;
   const bool valid = t < (int64_t)rows * per_row;
   const int row = valid ? (int)(t / per_row) : 0;
   const int rem = (int)(t - (int64_t)row * per_row);
-  const int hs = rem / qpv, qd = rem - hs * qpv;
-  const int width = a.N * Dh + 2 * a.G * Dh;
-  float4 x = valid ? *reinterpret_cast<const float4*>(a.raw + (int64_t)row * width + hs * Dh + 4 * qd)
-                   : make_float4(0.f, 0.f, 0.f, 0.f);
+  const int hs = valid ? rem / qpv : 0, qd = valid ? rem - hs * qpv : 0;
+  float4 x = *reinterpret_cast<const float4*>(a.raw + (int64_t)row * width + hs * Dh + 4 * qd);
   const bool is_q = hs < a.N;
-  if (!is_q && a.knorm_g) {  // KV-norm: RMSNorm over D_h with a learned gain
-    float ss = x.x * x.x + x.y * x.y + x.z * x.z + x.w * x.w;
-    for (int o = qpv / 2; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
-    const float r = rsqrtf(ss / Dh + a.eps);
-    const float4 gv = reinterpret_cast<const float4*>(a.knorm_g)[qd];
-    x = make_float4(x.x * r * gv.x, x.y * r * gv.y, x.z * r * gv.z, x.w * r * gv.w);
-  }
+  if (!is_q && a.knorm_g) x = kvnorm(x, a.knorm_g, qd);
   if (!valid) return;
   const int b = row / a.rows_per_batch, rb = row - b * a.rows_per_batch;
   if (a.rope) {
@@ -243,71 +280,40 @@ __global__ __launch_bounds__(256) void qk_post_kernel(QkvPostArgs a, int rows) {
   store4(a.k_ring, base + 4 * qd, x, a.out_kind);
 }
 
-// Values: one workgroup per 64 consecutive positions of one causal unit of one
-// stream and one KV group; KV-norm, then written transposed ([D_h][U_pad] per
-// slot) through LDS as rows of 64 positions.
-constexpr int VP_ROWS = 64;
-__global__ __launch_bounds__(256) void v_post_kernel(QkvPostArgs a, int blocks_per_unit) {
-  __shared__ float vt[64][VP_ROWS + 1];  // [dim][position]
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int Dh = a.Dh;
-  const bool act = lane < Dh;
-  const int g = blockIdx.y;
-  const int blk = blockIdx.x % blocks_per_unit, bu = blockIdx.x / blocks_per_unit;
-  const int units_per_batch = a.rows_per_batch / a.U;
-  const int lu = bu % units_per_batch, b = bu / units_per_batch;
-  const int pos0 = blk * VP_ROWS;
-  const int npos = min(VP_ROWS, a.U - pos0);
-  const int width = a.N * Dh + 2 * a.G * Dh;
-  constexpr int RPW = VP_ROWS / 4;
-  const int64_t row0 = (int64_t)b * a.rows_per_batch + (int64_t)lu * a.U + pos0 + wave * RPW;
-  float x[RPW];
-#pragma unroll
-  for (int i = 0; i < RPW; ++i)
-    x[i] = (act && wave * RPW + i < npos) ? a.raw[(row0 + i) * width + (a.N + a.G + g) * Dh + lane] : 0.f;
-#pragma unroll
-  for (int i = 0; i < RPW; ++i) {
-    float y = x[i];
-    if (a.vnorm_g) {
-      const float ms = wave_sum(y * y) / Dh;
-      y = act ? y * rsqrtf(ms + a.eps) * a.vnorm_g[lane] : 0.f;
-    }
-    vt[lane][wave * RPW + i] = y;
-  }
-  __syncthreads();
-  const int slot = (int)((a.u0 + lu) % a.S);
-  const int64_t vbase = ((int64_t)(b * a.G + g) * a.S + slot) * Dh * a.U_pad + pos0;
-  for (int d = wave; d < Dh; d += 4)
-    if (lane < npos) store_kind(a.vt_ring, vbase + (int64_t)d * a.U_pad + lane, vt[d][lane], a.out_kind);
-}
-
-// Temporal RoPE cos / sin of the call's (sub-)frames: entry (fs, pair) for
+// Temporal RoPE cos / sin of a stack's (sub-)frames: entry (fs, pair) for
 // position tau0 + fs; the angle is reduced modulo 2 pi in double precision so
 // that long streams keep full accuracy.
-__global__ void rope_time_kernel(int64_t tau0, int n_fs, int np, const int* axis,
-                                 const double* freq, float2* out) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n_fs * np) return;
+__device__ __forceinline__ void rope_time_entry(const RopeTimeArgs& a, int np, int i) {
   const int fs = i / np, pair = i - fs * np;
   float2 r = make_float2(1.f, 0.f);
-  if (axis[pair] == 0) {
-    const double ph = (double)(tau0 + fs) * freq[pair];
+  if (a.axis[pair] == 0) {
+    const double ph = (double)(a.tau0 + fs) * a.freq[pair];
     const double red = ph - 6.283185307179586 * floor(ph * 0.15915494309189535);
     float sn, cs;
     sincosf((float)red, &sn, &cs);
     r = make_float2(cs, sn);
   }
-  out[i] = r;
+  a.out[i] = r;
 }
 
+// The call's prologue in one launch: workgroups below rope_blocks fill the
+// temporal RoPE tables of both stacks, the others unshuffle the latents:
 // u[(b F + f) L + h W_t + w, c p^2 + i p + j] = z[b, c, f, p h + i, p w + j]; zero padding to K_pad.
-__global__ __launch_bounds__(256) void unshuffle_kernel(const void* z, int z_kind, int B, int C,
-                                                        int F, int H, int W, int p, int K_pad,
-                                                        void* u, int out_kind, int packed) {
+__global__ __launch_bounds__(256) void prologue_kernel(RopeTimeArgs r0, RopeTimeArgs r1, int np, int rope_blocks,
+                                                       const void* z, int z_kind, int B, int C,
+                                                       int F, int H, int W, int p, int K_pad,
+                                                       void* u, int out_kind, int packed) {
+  if ((int)blockIdx.x < rope_blocks) {
+    const int i = blockIdx.x * 256 + threadIdx.x, n0 = r0.n_fs * np, n1 = r1.n_fs * np;
+    if (i < n0) rope_time_entry(r0, np, i);
+    else if (i - n0 < n1) rope_time_entry(r1, np, i - n0);
+    return;
+  }
   const int Ht = H / p, Wt = W / p, L = Ht * Wt;
   const int64_t total = (int64_t)B * F * L * K_pad;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total;
-       e += (int64_t)gridDim.x * blockDim.x) {
+  const int64_t nblk = gridDim.x - rope_blocks;
+  for (int64_t e = (blockIdx.x - rope_blocks) * (int64_t)blockDim.x + threadIdx.x; e < total;
+       e += nblk * blockDim.x) {
     const int k = (int)(e % K_pad);
     const int64_t row = e / K_pad;
     float v = 0.f;
@@ -338,6 +344,54 @@ int grid_for(int64_t total) {
   return (int)(b < 65536 ? (b > 0 ? b : 1) : 65536);
 }
 
+struct NormLaunch {
+  const float* x;
+  int M, D;
+  const float *g, *b;
+  float eps;
+  void* out;
+  float* row_scale;
+  const float* static_sc;
+  unsigned* amax_out;
+  int packed;
+};
+
+template <int KIND, int OUT>
+hipError_t norm_width(const NormLaunch& n, hipStream_t s) {
+  auto launch = [&](auto nv, auto full) {
+    hipLaunchKernelGGL((norm_kernel<KIND, OUT, decltype(nv)::value, decltype(full)::value>), dim3((n.M + 3) / 4),
+                       dim3(256), 0, s, n.x, n.M, n.D, n.g, n.b, n.eps, n.out, n.row_scale, n.static_sc, n.amax_out,
+                       n.packed);
+    return hipGetLastError();
+  };
+  using std::integral_constant;
+  const std::true_type full{};
+  const std::false_type ragged{};
+  // the decoder widths (multiples of 256) unbranched, narrow ones with one
+  // vector per lane, any other with the general eight
+  if (n.D <= 256) return n.D == 256 ? launch(integral_constant<int, 1>{}, full) : launch(integral_constant<int, 1>{}, ragged);
+  switch (n.D) {
+    case 512: return launch(integral_constant<int, 2>{}, full);
+    case 768: return launch(integral_constant<int, 3>{}, full);
+    case 1024: return launch(integral_constant<int, 4>{}, full);
+    case 1280: return launch(integral_constant<int, 5>{}, full);
+    case 1536: return launch(integral_constant<int, 6>{}, full);
+    case 1792: return launch(integral_constant<int, 7>{}, full);
+    case 2048: return launch(integral_constant<int, 8>{}, full);
+    default: return launch(integral_constant<int, 8>{}, ragged);
+  }
+}
+
+template <int KIND>
+hipError_t norm_out(const NormLaunch& n, int out_kind, hipStream_t s) {
+  switch (out_kind) {
+    case 0: return norm_width<KIND, 0>(n, s);
+    case 1: return norm_width<KIND, 1>(n, s);
+    case 2: return norm_width<KIND, 2>(n, s);
+    default: return norm_width<KIND, 3>(n, s);
+  }
+}
+
 }  // namespace
 
 hipError_t norm_rows(const float* x, int M, int D, const float* g, const float* b, int kind,
@@ -347,14 +401,9 @@ hipError_t norm_rows(const float* x, int M, int D, const float* g, const float* 
   if (D % 4 || D > 2048 || (out_kind == 3 && !row_scale && !static_sc)) return hipErrorInvalidValue;
   if (packed && (out_kind == 3 ? D % 64 : (D % 32 || (out_kind != 0 && out_kind != 1))))
     return hipErrorInvalidValue;
-  const int grid = (M + 3) / 4;
-  if (kind == 0)
-    hipLaunchKernelGGL(norm_kernel<0>, dim3(grid), dim3(256), 0, s, x, M, D, g, b, eps, out, out_kind,
-                       row_scale, static_sc, amax_out, packed ? 1 : 0);
-  else
-    hipLaunchKernelGGL(norm_kernel<1>, dim3(grid), dim3(256), 0, s, x, M, D, g, b, eps, out, out_kind,
-                       row_scale, static_sc, amax_out, packed ? 1 : 0);
-  return hipGetLastError();
+  const NormLaunch n{x, M, D, g, b, eps, out, row_scale, static_sc, amax_out, packed ? 1 : 0};
+  if (kind == 0) return norm_out<0>(n, out_kind, s);
+  return norm_out<1>(n, out_kind, s);
 }
 
 hipError_t quant_rows_e4m3(const void* in, int in_kind, int64_t M, int K, uint8_t* codes,
@@ -371,33 +420,26 @@ hipError_t quant_rows_e4m3(const void* in, int in_kind, int64_t M, int K, uint8_
   return hipGetLastError();
 }
 
-hipError_t rope_time(const QkvPostArgs& a, hipStream_t s) {
-  if (!a.rope || a.rows_per_batch <= 0) return hipSuccess;
-  const int n_fs = a.rows_per_batch / a.L, np = a.Dh / 2;
-  hipLaunchKernelGGL(rope_time_kernel, dim3((n_fs * np + 255) / 256), dim3(256), 0, s, a.tau0,
-                     n_fs, np, a.rope_axis, a.rope_freq, a.rope_t);
-  return hipGetLastError();
-}
-
 hipError_t qkv_post(const QkvPostArgs& a, hipStream_t s) {
   const int rows = a.B * a.rows_per_batch;
   if (rows <= 0) return hipSuccess;
   if (a.Dh > 64 || a.Dh % 8 || a.rows_per_batch % a.U) return hipErrorInvalidValue;
   const int64_t threads = (int64_t)rows * (a.N + a.G) * (a.Dh / 4);
-  hipLaunchKernelGGL(qk_post_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, a, rows);
+  const int qk_blocks = (int)((threads + 255) / 256);
   const int blocks_per_unit = (a.U + VP_ROWS - 1) / VP_ROWS;
   const int units = a.B * (a.rows_per_batch / a.U);
-  hipLaunchKernelGGL(v_post_kernel, dim3(blocks_per_unit * units, a.G), dim3(256), 0, s, a,
-                     blocks_per_unit);
+  hipLaunchKernelGGL(qkv_post_kernel, dim3((unsigned)(qk_blocks + blocks_per_unit * units * a.G)), dim3(256), 0, s, a,
+                     rows, qk_blocks, blocks_per_unit);
   return hipGetLastError();
 }
 
-hipError_t unshuffle_latent(const void* z, int z_kind, int B, int C, int F, int H, int W, int p,
-                            int K_pad, void* u, int out_kind, hipStream_t s, bool packed) {
+hipError_t prologue(const void* z, int z_kind, int B, int C, int F, int H, int W, int p, int K_pad, void* u,
+                    int out_kind, bool packed, const RopeTimeArgs& r0, const RopeTimeArgs& r1, int np, hipStream_t s) {
   if (packed && (K_pad % 32 || (out_kind != 0 && out_kind != 1))) return hipErrorInvalidValue;
   const int64_t total = (int64_t)B * F * (H / p) * (W / p) * K_pad;
-  hipLaunchKernelGGL(unshuffle_kernel, dim3(grid_for(total)), dim3(256), 0, s, z, z_kind, B, C, F,
-                     H, W, p, K_pad, u, out_kind, packed ? 1 : 0);
+  const int rope_blocks = ((r0.n_fs + r1.n_fs) * np + 255) / 256;
+  hipLaunchKernelGGL(prologue_kernel, dim3(rope_blocks + grid_for(total)), dim3(256), 0, s, r0, r1, np, rope_blocks, z,
+                     z_kind, B, C, F, H, W, p, K_pad, u, out_kind, packed ? 1 : 0);
   return hipGetLastError();
 }
 
