@@ -97,9 +97,12 @@ struct GemmArgs {
 // Position of element (row, k) of an [N, K] weight in the packed layout the
 // 16-bit MFMA GEMM reads: 1 KB blocks of 16 rows x 32 K-columns, block-row
 // major, rows padded with zeros to a multiple of 16 (ceil(N / 16) 16 K
-// elements in all).
+// elements in all). Inside a block the 16-byte chunks of 8 columns come first,
+// then the rows: an MFMA fragment (8 columns of each of 16 rows per 16 lanes)
+// is 256 contiguous bytes, which a wave loads from memory as whole lines and
+// from LDS without bank conflicts.
 inline int64_t pack_w16_index(int64_t row, int64_t k, int64_t K) {
-  return ((row / 16) * (K / 32) + k / 32) * 512 + (row % 16) * 32 + k % 32;
+  return ((row / 16) * (K / 32) + k / 32) * 512 + k % 32 / 8 * 128 + (row % 16) * 8 + k % 8;
 }
 // The same layout for a 16-bit activation [M, K] that is a GEMM's A operand.
 // Each DMA of a K tile then reads one contiguous 1 KB block (eight whole

@@ -841,8 +841,8 @@ fd_status upload_weights(fd_decoder* dec, const void* w, int32_t wdt, size_t n_e
         const int64_t K = mat_k(t);
         host.assign(elems, 0.f);
         for (int64_t r = 0; r < t.s0; ++r)
-          for (int64_t k = 0; k < K; k += 32)  // runs of 32 K-columns stay contiguous
-            std::memcpy(&host[fd::pack_w16_index(r, k, K)], &src[r * K + k], 32 * sizeof(float));
+          for (int64_t k = 0; k < K; k += 8)  // runs of 8 K-columns stay contiguous
+            std::memcpy(&host[fd::pack_w16_index(r, k, K)], &src[r * K + k], 8 * sizeof(float));
         src.swap(host);
       }
       if (d.is16) {

@@ -11,11 +11,12 @@
 // gfx950 32x32x16 MFMA (fp32 accumulate). A and W are both K-contiguous; K
 // tiles of 32 columns are copied from memory straight into LDS by the buffer
 // unit (buffer_load ... lds, no register staging) several tiles ahead of the
-// MFMAs, and read back as MFMA fragments with 16-byte ds_read_b128 per lane
-// through a per-row XOR swizzle of the 16-byte chunks that keeps the 16 rows
-// one ds_read_b128 serves at once in 16 different bank groups.
+// MFMAs, and read back as MFMA fragments with 16-byte ds_read_b128 per lane.
+// Both operands are stored in fragment order (pack_w16_index), so the 16 rows
+// one ds_read_b128 serves at once are 256 contiguous bytes of LDS.
 #pragma once
 
+#include "gemm_small.h"
 #include "gemm_tile.h"
 
 namespace fd {
@@ -23,8 +24,8 @@ namespace {
 
 template <typename T, class C, int EPI>
 __global__ __launch_bounds__(C::NT, C::MIN_BLOCKS) void gemm_mfma_kernel(
-    const T* __restrict__ A, const T* __restrict__ W, int M, int N, int K, int lda, int ldw,
-    EpiParams ep, int tiles_m, int tiles_n, int vec_store, int a_packed) {
+    const T* __restrict__ A, const T* __restrict__ W, int M, int N, int K,
+    EpiParams ep, int tiles_m, int tiles_n, int vec_store) {
   constexpr int BM = C::BM, BN = C::BN, FM = C::FM, FN = C::FN, NS = C::NS, NW = C::NW;
   constexpr int QA = C::QA, Q = C::QA + C::QB, STAGE = C::STAGE;
   using V = typename Mfma<T>::V;
@@ -37,37 +38,25 @@ __global__ __launch_bounds__(C::NT, C::MIN_BLOCKS) void gemm_mfma_kernel(
   const int m0 = tm * BM, n0 = tn * BN;
   const int wm0 = (wave / C::WAVES_N) * C::WM, wn0 = (wave % C::WAVES_N) * C::WN;
 
-  // W is packed K-tile-major: blocks of 16 rows x 32 K-columns (1 KB), block
-  // (row / 16, k / 32) at ((row / 16) (K / 32) + k / 32) KB, rows padded with
-  // zeros to a multiple of 16, so each DMA of W reads one contiguous 1 KB
-  // block. A is row-major (lda), or packed the same way (lda = K, whole
-  // 16-row blocks readable).
+  // A and W are packed K-tile-major: blocks of 16 rows x 32 K-columns (1 KB),
+  // block (row / 16, k / 32) at ((row / 16) (K / 32) + k / 32) KB, in whole
+  // 16-row blocks, so each DMA reads one contiguous 1 KB block.
   const int KB = K / BKD;  // K tiles
-  const bool apk = a_packed != 0;
-  const int a_rows = apk ? (min(BM, M - m0) + 15) / 16 * 16 : min(BM, M - m0);
-  const __amdgpu_buffer_rsrc_t rA =
-      make_rsrc(A + (int64_t)m0 * lda, (uint32_t)a_rows * lda * (uint32_t)sizeof(T));
-  const uint32_t a_kstep = apk ? 1024u : (uint32_t)BKD * (uint32_t)sizeof(T);  // bytes per K tile
-  const int nrows_w = min(BN, (N + 15) / 16 * 16 - n0);
-  const __amdgpu_buffer_rsrc_t rB =
-      make_rsrc(W + (int64_t)(n0 / 16) * KB * 512, (uint32_t)(nrows_w / 16) * KB * 1024u);
-  (void)ldw;
-  // DMA j of this wave fills stage rows 16 q .. 16 q + 15, q = j NW + wave (A
-  // rows for j < QA, W rows after); lane l lands in row 16 q + l / 4, physical
-  // chunk l % 4, which holds K-chunk (l % 4) ^ ((l / 16) % 4).
-  const int lrow = lane >> 2, lchunk = (lane & 3) ^ ((lane >> 4) & 3);
+  const int nblk_a = min(BM / 16, (M + 15) / 16 - m0 / 16), nblk_w = min(BN / 16, (N + 15) / 16 - n0 / 16);
+  const __amdgpu_buffer_rsrc_t rA = make_rsrc(A + (int64_t)(m0 / 16) * KB * 512, (uint32_t)nblk_a * KB * 1024u);
+  const __amdgpu_buffer_rsrc_t rB = make_rsrc(W + (int64_t)(n0 / 16) * KB * 512, (uint32_t)nblk_w * KB * 1024u);
+  // DMA j of this wave fills block q = j NW + wave of the stage (A blocks for
+  // j < QA, W blocks after); lane l moves the block's 16 bytes at 16 l.
   uint32_t voff[Q];
 #pragma unroll
   for (int j = 0; j < Q; ++j) {
     const int q = j * NW + wave;
-    voff[j] = j >= QA ? (uint32_t)(q - BM / 16) * KB * 1024u + (uint32_t)(lrow * 64 + lchunk * 16)
-              : apk   ? (uint32_t)q * KB * 1024u + (uint32_t)(lrow * 64 + lchunk * 16)
-                      : (uint32_t)((16 * q + lrow) * lda + lchunk * 8) * (uint32_t)sizeof(T);
+    voff[j] = (uint32_t)(j >= QA ? q - BM / 16 : q) * KB * 1024u + (uint32_t)lane * 16u;
   }
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint4*)lds;
   // DMA instruction j of the refill of stage st with K tile kt
   auto dma1 = [&](int st, int kt, int j) {
-    const uint32_t soff = j < QA ? (uint32_t)kt * a_kstep : (uint32_t)kt * 1024u;
+    const uint32_t soff = (uint32_t)kt * 1024u;
     const uint32_t m0addr = lds0 + (uint32_t)(st * STAGE + 64 * (j * NW + wave)) * 16u;
     // M0 is reserved by the compiler, but nothing else in this kernel reads it
     // (no LDS DMA builtins, interpolation, GWS or message sends).
@@ -103,10 +92,11 @@ __global__ __launch_bounds__(C::NT, C::MIN_BLOCKS) void gemm_mfma_kernel(
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-  const int lr = lane & 31, lk = lane >> 5, xr = (lr >> 2) & 3;
-  // slot of fragment row (A: wm0 + lr, W: BM + wn0 + lr) at k-step ks: K-chunk 2 ks + lk
-  const int ia0 = (wm0 + lr) * 4 + (lk ^ xr), ia1 = (wm0 + lr) * 4 + ((2 + lk) ^ xr);
-  const int ib0 = (BM + wn0 + lr) * 4 + (lk ^ xr), ib1 = (BM + wn0 + lr) * 4 + ((2 + lk) ^ xr);
+  const int lr = lane & 31, lk = lane >> 5;
+  // slot of fragment row (A: wm0 + lr, W: BM + wn0 + lr) at k-step ks: chunk
+  // 2 ks + lk of its block
+  const int ia0 = (wm0 / 16 + (lr >> 4)) * 64 + lk * 16 + (lr & 15), ia1 = ia0 + 32;
+  const int ib0 = ((BM + wn0) / 16 + (lr >> 4)) * 64 + lk * 16 + (lr & 15), ib1 = ib0 + 32;
   V fa[2][FM], fb[2][FN];
   auto load_frags = [&](int slot, int st, int ks) {
     const uint4* sb = lds + st * STAGE;
@@ -205,18 +195,37 @@ __global__ __launch_bounds__(C::NT, C::MIN_BLOCKS) void gemm_mfma_kernel(
   }
 }
 
-template <typename T, class C, int EPI>
-hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
-  const int tm = (g.M + C::BM - 1) / C::BM, tn = (g.N + C::BN - 1) / C::BN;
-  // four consecutive output columns land contiguously and 16-byte aligned
-  // (fp32) / 8-byte aligned (16-bit) in the destination
+// Four consecutive output columns land contiguously and 16-byte aligned (fp32)
+// / 8-byte aligned (16-bit) in the destination.
+template <int EPI>
+bool vec_stores(const GemmArgs& g) {
   bool vec = g.N % 4 == 0 && g.ep.ld_out % 4 == 0;
   if (EPI == EPI_PIXEL || EPI == EPI_LINEAR_PIXEL) vec = vec && g.ep.s % 4 == 0;
   if (EPI == EPI_TUP) vec = vec && g.ep.dim % 4 == 0;
-  vec = vec && ((uintptr_t)g.ep.out_f % 16 == 0) && ((uintptr_t)g.ep.out_a % 8 == 0);
+  return vec && ((uintptr_t)g.ep.out_f % 16 == 0) && ((uintptr_t)g.ep.out_a % 8 == 0);
+}
+
+template <typename T, int FN, int PD, int EPI>
+hipError_t launch_direct(const GemmArgs& g, hipStream_t s) {
+  const int tm = (g.M + 31) / 32, tn = (g.N + 32 * FN - 1) / (32 * FN);
+  hipLaunchKernelGGL((gemm_direct_kernel<T, FN, PD, EPI>), dim3(tm * tn), dim3(64), 0, s, (const T*)g.A,
+                     (const T*)g.W, g.M, g.N, g.K, g.ep, tm, tn, vec_stores<EPI>(g) ? 1 : 0);
+  return hipGetLastError();
+}
+
+template <typename T, class C, int EPI>
+hipError_t launch_small(const GemmArgs& g, hipStream_t s) {
+  const int tm = (g.M + C::BM - 1) / C::BM, tn = (g.N + C::BN - 1) / C::BN;
+  hipLaunchKernelGGL((gemm_small_kernel<T, C, EPI>), dim3(tm * tn), dim3(C::NT), 0, s, (const T*)g.A, (const T*)g.W,
+                     g.M, g.N, g.K, g.ep, tm, tn, vec_stores<EPI>(g) ? 1 : 0);
+  return hipGetLastError();
+}
+
+template <typename T, class C, int EPI>
+hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
+  const int tm = (g.M + C::BM - 1) / C::BM, tn = (g.N + C::BN - 1) / C::BN;
   hipLaunchKernelGGL((gemm_mfma_kernel<T, C, EPI>), dim3(tm * tn), dim3(C::NT), 0, s,
-                     (const T*)g.A, (const T*)g.W, g.M, g.N, g.K, g.lda, g.ldw, g.ep, tm, tn, vec ? 1 : 0,
-                     g.a_packed);
+                     (const T*)g.A, (const T*)g.W, g.M, g.N, g.K, g.ep, tm, tn, vec_stores<EPI>(g) ? 1 : 0);
   return hipGetLastError();
 }
 
@@ -234,6 +243,21 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
 template <typename T, int EPI>
 hipError_t dispatch_tiles(const GemmArgs& g, hipStream_t s) {
   auto tiles = [&](int bm, int bn) { return ((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn); };
+  // Few output tiles: a wave per 32-row tile, then 2 x 2 waves through LDS (see
+  // gemm_small.h). Each line lies where the next kernel is as fast (us, this /
+  // next): residual adds of K = 6144 at 384 tiles of 32 x 32 21 / 28, at 624 28 /
+  // 24 (small), at 816 24 / 41, at 1584 48 / 42 (large); QKV (32 x 64 tiles, K =
+  // 1536) at 240 11 / 17, at 510 16 / 18, at 990 19 / 24, at 1470 21 / 24, at 2220
+  // 35 / 31; SwiGLU at 384 13 / 16, at 960 20 / 15.
+  if constexpr (EPI == EPI_QKV) {
+    if (tiles(32, 64) <= 640) return launch_direct<T, 2, 6, EPI>(g, s);
+    if (tiles(32, 64) <= 1600) return launch_small<T, SmallCfg<2, 2, 2, 2, 3>, EPI>(g, s);
+  } else if constexpr (EPI == EPI_SWIGLU) {
+    if (tiles(32, 64) <= 400) return launch_direct<T, 2, 6, EPI>(g, s);
+  } else {
+    if (tiles(32, 32) <= 500) return launch_direct<T, 1, 12, EPI>(g, s);
+    if (tiles(32, 32) <= 1000) return launch_small<T, SmallCfg<2, 2, 1, 4, 4>, EPI>(g, s);
+  }
   const bool short_rmw = EPI == EPI_RESID_ADD && g.K <= 2048;
   if (tiles(256, 256) >= 160 && !short_rmw) {
     // a SwiGLU projection of under two rounds of 256 x 256 tiles (the 480p

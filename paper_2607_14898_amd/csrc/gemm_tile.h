@@ -57,8 +57,8 @@ __device__ __forceinline__ void count_sat(unsigned* sat, int n) {
 // reshapes of the temporal upsampling (Eq. temporal_upsample) and of the
 // PixelShuffle store (Sec. 3.4 Step 3) are expressed this way, and so is the
 // packed operand layout of 16-bit activations (blocks of 16 rows x 32
-// columns: row part (row / 16) 16 ld + (row % 16) 32, column part
-// (col / 32) 512 + col % 32).
+// columns: row part (row / 16) 16 ld + (row % 16) 8, column part
+// (col / 32) 512 + (col % 32 / 8) 128 + col % 8).
 template <int EPI>
 constexpr bool kPackable = EPI == EPI_SWIGLU || EPI == EPI_STORE_ACT || EPI == EPI_STORE_SILU ||
                            EPI == EPI_STORE_GELU;
@@ -84,7 +84,7 @@ __device__ __forceinline__ int64_t row_off(const EpiParams& p, int row) {
     return ((int64_t)b * p.C * p.frames_out + fo) * OHW + (int64_t)p.s * h * OW + p.s * w;
   } else {
     if constexpr (kPackable<EPI>)
-      if (p.out_packed) return (int64_t)(row >> 4) * p.ld_out * 16 + (row & 15) * 32;
+      if (p.out_packed) return (int64_t)(row >> 4) * p.ld_out * 16 + (row & 15) * 8;
     return (int64_t)row * p.ld_out;
   }
 }
@@ -108,7 +108,7 @@ __device__ __forceinline__ int64_t col_off(const EpiParams& p, int col) {
     return ((int64_t)c3 * p.frames_out + j) * OHW + (int64_t)i1 * OW + i2;
   } else {
     if constexpr (kPackable<EPI>)
-      if (p.out_packed) return (int64_t)(col >> 5) * 512 + (col & 31);
+      if (p.out_packed) return (int64_t)(col >> 5) * 512 + ((col >> 3) & 3) * 128 + (col & 7);
     return col;
   }
 }
@@ -286,6 +286,9 @@ __device__ __forceinline__ void store_tile(const EpiParams& ep, const f32x16 (&a
         wl[rr * LS + 32 + lr] = acc[i][1][r] + bias1;
       }
       __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this wave's LDS writes are done
+      // (unrolled where one block is all a wave has: the rows' table loads then
+      // overlap, which is half of a small call's projection)
+#pragma clang loop unroll_count(FM == 1 ? 8 : 1)
       for (int it = 0; it < 8; ++it) {
         const int rr = it * 4 + (lane >> 4);
         const int row_t = rbase + rr, row = min(row_t, M - 1);
@@ -614,8 +617,8 @@ __device__ __forceinline__ void store_tile_t(const EpiParams& ep, const f32x16 (
 // with buffer_load_dwordx4 ... lds (no register staging, no LDS store
 // instructions), NS tiles deep: while tile t is multiplied, tiles t + 1 ..
 // t + NS - 1 are in flight. A DMA instruction writes the 16 bytes of lane l to
-// LDS slot l after a wave-uniform base, so the bank swizzle is applied on the
-// global side: lane l fetches the chunk that belongs in slot l.
+// LDS slot l after a wave-uniform base; the operands are stored in fragment
+// order, so a 1 KB block lands in LDS as it is read.
 // ---------------------------------------------------------------------------
 constexpr int BKD = 32;  // K-columns per stage: 4 chunks of 16 bytes per row
 
@@ -643,10 +646,6 @@ struct TileCfg {
 #define FD_VMCNT(n) ((((n) & 0xF) | ((((n) >> 4) & 3) << 14) | (0x7 << 4) | (0xF << 8)))
 #define FD_LGKMCNT0 (0xF | (0x3 << 14) | (0x7 << 4))
 
-// Stage row r (A rows 0..BM-1, then W rows) holds K-chunk c of that row in
-// physical slot 4 r + (c ^ ((r / 4) % 4)): the 16 rows one ds_read_b128 serves
-// at once then cover all 16 bank groups.
-//
 // The DMAs are issued from inline assembly (M0 = LDS destination of the wave),
 // so the compiler neither sees nor orders them; every ordering they need is
 // explicit: s_waitcnt on the wave's own DMAs, then s_barrier (with compiler

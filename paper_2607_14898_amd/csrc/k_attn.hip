@@ -377,9 +377,10 @@ __global__ __launch_bounds__(256, NQB == 2 ? 2 : 3) void attn_mfma_kernel(AttnAr
       // row-major, or the O projection's packed operand layout (blocks of 16
       // rows x 32 columns; the head's two 32-column halves are blocks 2n, 2n + 1)
       const int64_t orow = qrow(qb);
-      T* op = (T*)a.o + (a.o_packed ? (orow >> 4) * ldq * 16 + (orow & 15) * 32 + (int64_t)n * 1024
+      // (in a block, 8-column chunks before rows: 16 lanes write 256 bytes in a row)
+      T* op = (T*)a.o + (a.o_packed ? (orow >> 4) * ldq * 16 + (orow & 15) * 8 + (int64_t)n * 1024
                                     : orow * ldq + n * 64);
-      const int dstep = a.o_packed ? 512 : 32;
+      const int dstep = a.o_packed ? 512 : 32, rstep = a.o_packed ? 128 : 8;
 #pragma unroll
       for (int d = 0; d < 2; ++d)
 #pragma unroll
@@ -388,7 +389,7 @@ __global__ __launch_bounds__(256, NQB == 2 ? 2 : 3) void attn_mfma_kernel(AttnAr
           E o4[4];
 #pragma unroll
           for (int e = 0; e < 4; ++e) o4[e] = M::cvt(acc[qb][d][r4 * 4 + e] * inv);
-          *reinterpret_cast<uint2*>(op + d * dstep + 8 * r4 + 4 * lh) = *reinterpret_cast<uint2*>(o4);
+          *reinterpret_cast<uint2*>(op + d * dstep + rstep * r4 + 4 * lh) = *reinterpret_cast<uint2*>(o4);
         }
     }
   }

@@ -25,9 +25,10 @@ __device__ __forceinline__ void store_kind(void* out, int64_t i, float v, int ki
 }
 
 // Element (row, k) of a 16-bit [rows, K] activation in the packed operand
-// layout of the MFMA GEMM (blocks of 16 rows x 32 columns, block-row major).
+// layout of the MFMA GEMM (blocks of 16 rows x 32 columns, block-row major,
+// inside a block 8-column chunks, then rows).
 __device__ __forceinline__ int64_t pk16(int64_t row, int k, int K) {
-  return ((row >> 4) * (K >> 5) + (k >> 5)) * 512 + (row & 15) * 32 + (k & 31);
+  return ((row >> 4) * (K >> 5) + (k >> 5)) * 512 + ((k >> 3) & 3) * 128 + (row & 15) * 8 + (k & 7);
 }
 // Byte (row, k) of E4M3 codes [rows, K] in the packed operand layout of the
 // FP8 GEMM (blocks of 16 rows x 64 bytes).
