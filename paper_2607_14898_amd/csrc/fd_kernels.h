@@ -28,7 +28,7 @@ enum Epi : int {
 
 struct QkvPostArgs {
   const float* raw = nullptr;  // [rows, D + 2 G D_h]
-  void* q = nullptr;           // [rows, N D_h]
+  void* q = nullptr;           // queries: fp32 [rows, N D_h]; 16-bit [N][8][rows][8] (see AttnArgs)
   void* k_ring = nullptr;
   void* vt_ring = nullptr;
   const float* knorm_g = nullptr;  // [D_h] or null
@@ -139,7 +139,9 @@ hipError_t gemm_fp8(const GemmArgs& g, hipStream_t stream);
 
 // Attention over the rolling KV ring.
 struct AttnArgs {
-  const void* q = nullptr;     // [rows, N * D_h], rows = B * n_units * U
+  // [rows, N * D_h], rows = B * n_units * U; 16-bit path: [N][8][rows][8], the
+  // 8-column chunks of a head vector before the rows
+  const void* q = nullptr;
   const void* k_ring = nullptr;// [B][G][S][U_pad][D_h]
   const void* vt_ring = nullptr;// [B][G][S][D_h][U_pad]
   void* o = nullptr;           // [rows, N * D_h]; 16-bit path: packed (pack_a16_index) if o_packed

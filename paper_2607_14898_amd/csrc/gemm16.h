@@ -177,7 +177,6 @@ __global__ __launch_bounds__(C::NT, C::MIN_BLOCKS) void gemm_mfma_kernel(
     sc = sn;
   }
   mfmas(1);
-  static_assert(EPI != EPI_QKV || NW * 32 * 68 * 4 <= NS * STAGE * 16, "QKV epilogue staging fits the stage buffers");
   if constexpr (kTransposed<EPI>)
     store_tile_t<EPI, T, FM, FN>(ep, acc, m0 + wm0, n0 + wn0, M, N, lr, lk, vec_store != 0);
   else if constexpr (EPI == EPI_PIXEL || EPI == EPI_LINEAR_PIXEL) {
@@ -185,13 +184,11 @@ __global__ __launch_bounds__(C::NT, C::MIN_BLOCKS) void gemm_mfma_kernel(
     // per store makes the epilogue loops too large to unroll, and the
     // accumulators would go to scratch memory)
     constexpr bool R = !(C::NW == 4 && C::MIN_BLOCKS == 1);
-    float* ws = reinterpret_cast<float*>(lds);
-    if (ep.out_fmt == 0) store_tile<EPI, T, FM, FN, R, 0>(ep, acc, m0 + wm0, n0 + wn0, M, N, lr, lk, ws);
-    else if (ep.out_fmt == 1) store_tile<EPI, T, FM, FN, R, 1>(ep, acc, m0 + wm0, n0 + wn0, M, N, lr, lk, ws);
-    else store_tile<EPI, T, FM, FN, R, 2>(ep, acc, m0 + wm0, n0 + wn0, M, N, lr, lk, ws);
+    if (ep.out_fmt == 0) store_tile<EPI, T, FM, FN, R, 0>(ep, acc, m0 + wm0, n0 + wn0, M, N, lr, lk);
+    else if (ep.out_fmt == 1) store_tile<EPI, T, FM, FN, R, 1>(ep, acc, m0 + wm0, n0 + wn0, M, N, lr, lk);
+    else store_tile<EPI, T, FM, FN, R, 2>(ep, acc, m0 + wm0, n0 + wn0, M, N, lr, lk);
   } else {
-    store_tile<EPI, T, FM, FN, !(C::NW == 4 && C::MIN_BLOCKS == 1)>(ep, acc, m0 + wm0, n0 + wn0, M, N, lr, lk,
-                                                                   reinterpret_cast<float*>(lds));
+    store_tile<EPI, T, FM, FN, !(C::NW == 4 && C::MIN_BLOCKS == 1)>(ep, acc, m0 + wm0, n0 + wn0, M, N, lr, lk);
   }
 }
 

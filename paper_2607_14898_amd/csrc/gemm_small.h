@@ -27,18 +27,18 @@
 namespace fd {
 namespace {
 
-// Epilogue of one wave's 32 x 32 FN block (ws: its LDS for the QKV post step).
+// Epilogue of one wave's 32 x 32 FN block.
 template <int EPI, typename T, int FN>
 __device__ __forceinline__ void store_small(const EpiParams& ep, const f32x16 (&acc)[1][FN], int r0, int c0, int M,
-                                            int N, int lr, int lk, bool vec, float* ws) {
+                                            int N, int lr, int lk, bool vec) {
   if constexpr (kTransposed<EPI>)
     store_tile_t<EPI, T, 1, FN>(ep, acc, r0, c0, M, N, lr, lk, vec);
   else if constexpr (EPI == EPI_PIXEL || EPI == EPI_LINEAR_PIXEL) {
-    if (ep.out_fmt == 0) store_tile<EPI, T, 1, FN, true, 0>(ep, acc, r0, c0, M, N, lr, lk, ws);
-    else if (ep.out_fmt == 1) store_tile<EPI, T, 1, FN, true, 1>(ep, acc, r0, c0, M, N, lr, lk, ws);
-    else store_tile<EPI, T, 1, FN, true, 2>(ep, acc, r0, c0, M, N, lr, lk, ws);
+    if (ep.out_fmt == 0) store_tile<EPI, T, 1, FN, true, 0>(ep, acc, r0, c0, M, N, lr, lk);
+    else if (ep.out_fmt == 1) store_tile<EPI, T, 1, FN, true, 1>(ep, acc, r0, c0, M, N, lr, lk);
+    else store_tile<EPI, T, 1, FN, true, 2>(ep, acc, r0, c0, M, N, lr, lk);
   } else {
-    store_tile<EPI, T, 1, FN, true>(ep, acc, r0, c0, M, N, lr, lk, ws);
+    store_tile<EPI, T, 1, FN, true>(ep, acc, r0, c0, M, N, lr, lk);
   }
 }
 
@@ -50,7 +50,6 @@ __global__ __launch_bounds__(64, 1) void gemm_direct_kernel(const T* __restrict_
                                                             int vec_store) {
   using V = typename Mfma<T>::V;
   typedef unsigned u4 __attribute__((ext_vector_type(4)));
-  __shared__ __attribute__((aligned(16))) float ws[EPI == EPI_QKV ? 32 * 68 : 1];  // the QKV epilogue's staging
   const int lane = threadIdx.x;
   int tm, tn;
   tile_of(blockIdx.x, tiles_m * tiles_n, tiles_m, tiles_n, tm, tn);
@@ -105,7 +104,7 @@ __global__ __launch_bounds__(64, 1) void gemm_direct_kernel(const T* __restrict_
 #pragma unroll
   for (int p = 0; p < PD; ++p)
     if (base + p < KB) mul(p);
-  store_small<EPI, T, FN>(ep, acc, m0, n0, M, N, lr, lk, vec_store != 0, ws);
+  store_small<EPI, T, FN>(ep, acc, m0, n0, M, N, lr, lk, vec_store != 0);
 }
 
 // WAVES_M x WAVES_N waves of 32 x 32 FN; NS stages of KS 32-column K tiles.
@@ -259,8 +258,7 @@ __global__ __launch_bounds__(C::NT, 1) void gemm_small_kernel(const T* __restric
       mfma1(0, 2 * sub);
       mfma1(0, 2 * sub + 1);
     }
-  static_assert(EPI != EPI_QKV || NW * 32 * 68 * 4 <= NS * C::STAGE * 16, "QKV epilogue staging fits the stage buffers");
-  store_small<EPI, T, FN>(ep, acc, m0 + wm0, n0 + wn0, M, N, lr, lk, vec_store != 0, reinterpret_cast<float*>(lds));
+  store_small<EPI, T, FN>(ep, acc, m0 + wm0, n0 + wn0, M, N, lr, lk, vec_store != 0);
 }
 
 }  // namespace

@@ -223,136 +223,18 @@ __device__ __forceinline__ void tile_of(int bid, int n_tiles, int tiles_m, int t
 // before any of its stores: interleaved, every load would wait for the store
 // before it (the compiler cannot tell the addresses apart) and each element
 // would cost a full memory round trip.
-// x / d for 0 <= x < 2^23 and 0 < d, given inv = 1.0f / d (float product, then
-// one exact integer correction)
+// x / d for 0 <= x < 2^23 and 0 < d < 2^23, given inv = 1.0f / d (float product,
+// then one exact integer correction; the products fit 24 bits)
 __device__ __forceinline__ int div_small(int x, int d, float inv) {
   int q = (int)((float)x * inv);
-  const int r = x - q * d;
+  const int r = x - __mul24(q, d);
   return q + (r >= d) - (r < 0);
 }
 
 template <int EPI, typename T, int FM, int FN, bool FAST_RMW, int PXF = 0>
 __device__ __forceinline__ void store_tile(const EpiParams& ep, const f32x16 (&acc)[FM][FN], int r0,
-                                           int c0, int M, int N, int lr, int lk, float* ws) {
-  if constexpr (EPI == EPI_QKV) {
-    // The QKV projection's post step (Sec. 3.2, Eq. kv_cache): a wave's 64
-    // columns are one head vector (head slot c0 / 64: query heads, then key
-    // groups, then value groups). Each 32-row block of the wave goes through
-    // the wave's share of the stage buffers (free once the K loop is done): 16 lanes then hold
-    // 4 columns of one row, so the KV-norm (RMS over the 64 columns) is a
-    // 16-lane sum and the 3D-RoPE pairs sit inside a lane. Queries go to the
-    // query buffer, keys to their ring slot, values (normalised in LDS, then
-    // one lane per column) transposed to the V ring.
-    static_assert(FN == 2, "one 64-column head vector per wave");
-    const QkvPostArgs& a = ep.qkv;
-    const int lane = lk * 32 + lr;
-    const int wave = threadIdx.x >> 6;
-    const int hs = c0 >> 6;
-    const bool is_q = hs < a.N, is_v = hs >= a.N + a.G;
-    const float* gn = is_q ? nullptr : (is_v ? a.vnorm_g : a.knorm_g);
-    const int kvg = hs - a.N - (is_v ? a.G : 0);  // KV group
-    const int cq = 4 * (lane & 15);               // this lane's 4 columns in the second pass
-    float4 gq = make_float4(1.f, 1.f, 1.f, 1.f);
-    if (gn) gq = *reinterpret_cast<const float4*>(gn + cq);
-    const bool rope = a.rope && !is_v;
-    const int pa = cq >> 1;  // RoPE pairs pa and pa + 1 of columns cq .. cq + 3
-    const int ax0 = rope ? a.rope_axis[pa] : 0, ax1 = rope ? a.rope_axis[pa + 1] : 0;
-    const float inv_rpb = 1.f / a.rows_per_batch, inv_L = 1.f / a.L;
-    const float inv_gw = 1.f / a.grid_w, inv_U = 1.f / a.U;
-    const int slot0 = (int)(a.u0 % a.S);
-    const float bias0 = ep.bias[min(c0, N - 64) + lr], bias1 = ep.bias[min(c0, N - 64) + 32 + lr];
-    constexpr int LS = 68;  // row stride: rows 4 apart fall in other banks, rows stay 16-byte aligned
-    float* wl = ws + wave * (32 * LS);  // [32 rows][64 columns]
-    // row of the call -> (stream, unit, position) and (sub-frame, h, w)
-    auto split = [&](int row, int& b, int& lu, int& pos, int& fs, int& hh, int& ww) {
-      b = div_small(row, a.rows_per_batch, inv_rpb);
-      const int rb = row - b * a.rows_per_batch;
-      lu = div_small(rb, a.U, inv_U);
-      pos = rb - lu * a.U;
-      fs = div_small(rb, a.L, inv_L);
-      const int tok = rb - fs * a.L;
-      hh = div_small(tok, a.grid_w, inv_gw);
-      ww = tok - hh * a.grid_w;
-    };
-    __syncthreads();  // every wave is past its last read of the stage buffers
-    if (c0 >= N) return;
-#pragma unroll
-    for (int i = 0; i < FM; ++i) {
-      const int rbase = r0 + i * 32;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int rr = 8 * (r >> 2) + 4 * lk + (r & 3);
-        wl[rr * LS + lr] = acc[i][0][r] + bias0;
-        wl[rr * LS + 32 + lr] = acc[i][1][r] + bias1;
-      }
-      __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this wave's LDS writes are done
-      // (unrolled where one block is all a wave has: the rows' table loads then
-      // overlap, which is half of a small call's projection)
-#pragma clang loop unroll_count(FM == 1 ? 8 : 1)
-      for (int it = 0; it < 8; ++it) {
-        const int rr = it * 4 + (lane >> 4);
-        const int row_t = rbase + rr, row = min(row_t, M - 1);
-        float4 v = *reinterpret_cast<const float4*>(wl + rr * LS + cq);
-        if (gn) {
-          float ss = v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
-#pragma unroll
-          for (int o = 1; o < 16; o <<= 1) ss += __shfl_xor(ss, o);
-          const float rn = rsqrtf(ss * (1.f / 64.f) + a.eps);
-          v = make_float4(v.x * rn * gq.x, v.y * rn * gq.y, v.z * rn * gq.z, v.w * rn * gq.w);
-        }
-        int b, lu, pos, fs, hh, ww;
-        split(row, b, lu, pos, fs, hh, ww);
-        if (rope) {
-          const float2 c0v = ax0 == 0 ? a.rope_t[fs * 32 + pa] : a.rope_hw[(ax0 == 1 ? hh : ww) * 32 + pa];
-          const float2 c1v = ax1 == 0 ? a.rope_t[fs * 32 + pa + 1] : a.rope_hw[(ax1 == 1 ? hh : ww) * 32 + pa + 1];
-          v = make_float4(v.x * c0v.x - v.y * c0v.y, v.x * c0v.y + v.y * c0v.x,
-                          v.z * c1v.x - v.w * c1v.y, v.z * c1v.y + v.w * c1v.x);
-        }
-        if (is_v) {  // normalised values back to LDS for the transposed store
-          *reinterpret_cast<float4*>(wl + rr * LS + cq) = v;
-          continue;
-        }
-        if (row_t >= M) continue;
-        T o4[4] = {to_act<T>(v.x), to_act<T>(v.y), to_act<T>(v.z), to_act<T>(v.w)};
-        T* dst;
-        if (is_q) {
-          dst = (T*)a.q + (int64_t)row * (a.N * 64) + c0 + cq;
-        } else {
-          const int slot = (slot0 + lu) % a.S;
-          dst = (T*)a.k_ring + (((int64_t)(b * a.G + kvg) * a.S + slot) * a.U_pad + pos) * 64 + cq;
-        }
-        *reinterpret_cast<uint2*>(dst) = *reinterpret_cast<const uint2*>(o4);
-      }
-      if (is_v) {  // V^T[dim][pos] of the block's 32 rows
-        // lane l % 16 takes rows 2 (l % 16) and 2 (l % 16) + 1, lane / 16 picks
-        // the dimension: each store instruction writes 32 consecutive positions
-        // of 4 dimensions (four 64-byte segments), as 4-byte pairs where the
-        // two rows are adjacent in one ring slot
-        __builtin_amdgcn_s_waitcnt(0xC07F);
-        const int l16 = lane & 15, dg = lane >> 4;
-        const int ra = rbase + 2 * l16;
-        const bool oka = ra < M, okb = ra + 1 < M;
-        int b0, lu0, pos0, b1, lu1, pos1, fs, hh, ww;
-        split(min(ra, M - 1), b0, lu0, pos0, fs, hh, ww);
-        split(min(ra + 1, M - 1), b1, lu1, pos1, fs, hh, ww);
-        T* va = (T*)a.vt_ring + ((int64_t)(b0 * a.G + kvg) * a.S + (slot0 + lu0) % a.S) * 64 * a.U_pad + pos0;
-        T* vb = (T*)a.vt_ring + ((int64_t)(b1 * a.G + kvg) * a.S + (slot0 + lu1) % a.S) * 64 * a.U_pad + pos1;
-        const bool pair = oka && okb && vb == va + 1 && (pos0 & 1) == 0;
-#pragma unroll 4
-        for (int it = 0; it < 16; ++it) {
-          const int d = it * 4 + dg;
-          const T x0 = to_act<T>(wl[(2 * l16) * LS + d]), x1 = to_act<T>(wl[(2 * l16 + 1) * LS + d]);
-          if (pair) {
-            *reinterpret_cast<uint32_t*>(va + (int64_t)d * a.U_pad) = bits16(x0) | (bits16(x1) << 16);
-          } else {
-            if (oka) va[(int64_t)d * a.U_pad] = x0;
-            if (okb) vb[(int64_t)d * a.U_pad] = x1;
-          }
-        }
-      }
-      __builtin_amdgcn_s_waitcnt(0xC07F);  // the block's LDS reads are done before the next block
-    }
-  } else if constexpr (EPI == EPI_SWIGLU) {
+                                           int c0, int M, int N, int lr, int lk) {
+  if constexpr (EPI == EPI_SWIGLU) {
     float bg[FN / 2], bu[FN / 2];
 #pragma unroll
     for (int j = 0; j < FN; j += 2) {
@@ -455,6 +337,144 @@ __device__ __forceinline__ void store_tile(const EpiParams& ep, const f32x16 (&a
   }
 }
 
+// The QKV projection's post step (Sec. 3.2, Eq. kv_cache) on transposed
+// accumulators: a wave's 64 columns are one head vector (head slot c0 / 64:
+// query heads, then key groups, then value groups), and a lane holds 32 of one
+// row's 64 values in groups of 4 consecutive columns 32 j + 8 q + 4 lk (its other
+// half, lane ^ 32, holds the rest). So the row's position is worked out once per
+// lane, the 3D-RoPE pairs sit inside a lane, and the KV-norm's sum of squares
+// takes one exchange per group (summed as a tree over the 16 groups). Queries
+// go to the query buffer in 8-column chunks (chunk-major, then rows: 32 lanes
+// write 512 bytes in a row, and the attention reads them so), normalised and
+// rotated keys to their ring slot, normalised values to the V^T ring with
+// neighbouring lanes' positions paired into 4-byte stores.
+// (Through LDS, 16 lanes to a row, this step took about 4 us of a small call's
+// launch: 11.3 us for 130 rows of the XL projection.)
+template <typename T, int FM>
+__device__ __forceinline__ void store_qkv(const EpiParams& ep, const f32x16 (&acc)[FM][2], int r0, int c0, int M, int N,
+                                          int lr, int lk) {
+  if (c0 >= N) return;
+  const QkvPostArgs& a = ep.qkv;
+  const int hs = c0 >> 6;
+  const bool is_q = hs < a.N, is_v = hs >= a.N + a.G;
+  const float* gn = is_q ? nullptr : (is_v ? a.vnorm_g : a.knorm_g);
+  const int kvg = hs - a.N - (is_v ? a.G : 0);  // KV group
+  const float inv_rpb = 1.f / a.rows_per_batch, inv_L = 1.f / a.L;
+  const float inv_gw = 1.f / a.grid_w, inv_U = 1.f / a.U;
+  const int slot0 = (int)(a.u0 % a.S);
+  float4 bias[2][4];
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) bias[j][q] = *reinterpret_cast<const float4*>(ep.bias + c0 + 32 * j + 8 * q + 4 * lk);
+#pragma unroll
+  for (int i = 0; i < FM; ++i) {
+    const int row_t = r0 + i * 32 + lr, row = min(row_t, M - 1);
+    const bool ok = row_t < M;
+    float4 v[2][4];
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        v[j][q] = make_float4(acc[i][j][4 * q] + bias[j][q].x, acc[i][j][4 * q + 1] + bias[j][q].y,
+                              acc[i][j][4 * q + 2] + bias[j][q].z, acc[i][j][4 * q + 3] + bias[j][q].w);
+    if (gn) {
+      float ss[2][4];
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const float4 x = v[j][q];
+          ss[j][q] = x.x * x.x + x.y * x.y + x.z * x.z + x.w * x.w;
+          ss[j][q] += __shfl_xor(ss[j][q], 32);
+        }
+      const float sum = ((ss[0][0] + ss[0][1]) + (ss[0][2] + ss[0][3])) + ((ss[1][0] + ss[1][1]) + (ss[1][2] + ss[1][3]));
+      const float rn = rsqrtf(sum * (1.f / 64.f) + a.eps);
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const float4 g4 = *reinterpret_cast<const float4*>(gn + 32 * j + 8 * q + 4 * lk);
+          const float4 x = v[j][q];
+          v[j][q] = make_float4(x.x * rn * g4.x, x.y * rn * g4.y, x.z * rn * g4.z, x.w * rn * g4.w);
+        }
+    }
+    // row of the call -> stream and row of the stream; (unit, position) and
+    // (sub-frame, h, w) from that
+    const int b = div_small(row, a.rows_per_batch, inv_rpb);
+    const int rb = row - __mul24(b, a.rows_per_batch);
+    if (a.rope && !is_v) {
+      const int fs = div_small(rb, a.L, inv_L), tok = rb - __mul24(fs, a.L);
+      const int hh = div_small(tok, a.grid_w, inv_gw), ww = tok - __mul24(hh, a.grid_w);
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          // RoPE pairs pa and pa + 1 of this group; an axis boundary may lie between them
+          const int pa = 16 * j + 4 * q + 2 * lk;
+          const int ax0 = a.rope_axis[pa], ax1 = a.rope_axis[pa + 1];
+          const float2 c0v = ax0 == 0 ? a.rope_t[fs * 32 + pa] : a.rope_hw[(ax0 == 1 ? hh : ww) * 32 + pa];
+          const float2 c1v = ax1 == 0 ? a.rope_t[fs * 32 + pa + 1] : a.rope_hw[(ax1 == 1 ? hh : ww) * 32 + pa + 1];
+          const float4 x = v[j][q];
+          v[j][q] = make_float4(x.x * c0v.x - x.y * c0v.y, x.x * c0v.y + x.y * c0v.x,
+                                x.z * c1v.x - x.w * c1v.y, x.z * c1v.y + x.w * c1v.x);
+        }
+    }
+    auto pack4 = [](float4 x) {
+      return make_uint2(bits16(to_act<T>(x.x)) | (bits16(to_act<T>(x.y)) << 16),
+                        bits16(to_act<T>(x.z)) | (bits16(to_act<T>(x.w)) << 16));
+    };
+    if (is_q) {
+      if (!ok) continue;
+      T* dst = (T*)a.q + ((int64_t)hs * 8 * M + row) * 8 + 4 * lk;
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) *reinterpret_cast<uint2*>(dst + (int64_t)(4 * j + q) * M * 8) = pack4(v[j][q]);
+      continue;
+    }
+    const int lu = div_small(rb, a.U, inv_U), pos = rb - __mul24(lu, a.U);
+    const int sl = slot0 + lu;  // (below 2 S: a call has at most S units)
+    const int64_t kv = (int64_t)(b * a.G + kvg) * a.S + (sl >= a.S ? sl - a.S : sl);  // ring slot
+    if (!is_v) {
+      if (!ok) continue;
+      T* dst = (T*)a.k_ring + (kv * a.U_pad + pos) * 64 + 4 * lk;
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) *reinterpret_cast<uint2*>(dst + 32 * j + 8 * q) = pack4(v[j][q]);
+      continue;
+    }
+    // V^T[dim][pos]: lanes 2 m and 2 m + 1 hold neighbouring rows; where these are
+    // an aligned pair of positions of one slot (rows stay in order, so only a
+    // unit's end or an odd start breaks a pair), the even lane stores both of
+    // dimension d, the odd lane both of d + 1
+    const int odd = lr & 1;
+    const int pos_e = odd ? pos - 1 : pos;  // the pair's first position
+    const bool pair = (row_t | 1) < M && (pos_e & 1) == 0 && pos_e >= 0 && pos_e + 1 < a.U;
+    T* vt = (T*)a.vt_ring + kv * 64 * a.U_pad;
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const uint2 w = pack4(v[j][q]);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {  // dimensions d and d + 1
+          const int d = 32 * j + 8 * q + 4 * lk + 2 * h;
+          const uint32_t own = h ? w.y : w.x;
+          const uint32_t oth = (uint32_t)__shfl_xor((int)own, 1);
+          if (pair) {
+            const uint32_t x = odd ? (oth >> 16) | (own & 0xFFFF0000u) : (own & 0xFFFFu) | (oth << 16);
+            *reinterpret_cast<uint32_t*>(vt + (int64_t)(d + odd) * a.U_pad + pos_e) = x;
+          } else if (ok) {
+            vt[(int64_t)d * a.U_pad + pos] = __builtin_bit_cast(T, (uint16_t)(own & 0xFFFFu));
+            vt[(int64_t)(d + 1) * a.U_pad + pos] = __builtin_bit_cast(T, (uint16_t)(own >> 16));
+          }
+        }
+      }
+  }
+}
+
 // Epilogue of one wave's blocks computed transposed (acc[i][j] = W block j
 // times A block i): lane (lk, lr) holds output row r0 + 32 i + lr and, in
 // registers 4 q .. 4 q + 3, the four consecutive columns c0 + 32 j + 8 q +
@@ -468,6 +488,10 @@ __device__ __forceinline__ void store_tile_t(const EpiParams& ep, const f32x16 (
   // column's then its row's dequantisation scale right before use
   static_assert(!SCALED || EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_E4M3, "scaled transposed epilogue: SwiGLU only");
   typedef __attribute__((ext_vector_type(4))) float f4;
+  if constexpr (EPI == EPI_QKV) {
+    store_qkv<T, FM>(ep, acc, r0, c0, M, N, lr, lk);
+    return;
+  }
   int nsat = 0;  // fp16 values clamped to +-65504 by this lane
   int64_t ro[FM];
   bool rok[FM];
@@ -654,7 +678,7 @@ struct TileCfg {
 // consecutive columns per lane make one 8-byte store and one bias / SiLU pass
 // per four values. fp32 destinations keep the direct layout, where the 32 lanes
 // of a half-wave write one full 128-byte row segment per store.
-template <int EPI> constexpr bool kTransposed = EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_E4M3 ||
+template <int EPI> constexpr bool kTransposed = EPI == EPI_QKV || EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_E4M3 ||
     EPI == EPI_STORE_ACT || EPI == EPI_STORE_SILU || EPI == EPI_STORE_GELU;
 
 using TileL = TileCfg<256, 256, 2, 4, 4, true>;   // 8 waves of 128 x 64, 128 KB LDS

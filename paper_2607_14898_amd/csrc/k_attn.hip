@@ -110,6 +110,7 @@ __global__ __launch_bounds__(256, NQB == 2 ? 2 : 3) void attn_mfma_kernel(AttnAr
   const int64_t u = a.u0 + lu;
   const int ldq = a.N * 64;
   const int q0 = qt * QB + (wave / HPB) * QW;  // first query (unit-local) of this wave
+  const int64_t q_rows = (int64_t)a.B * a.n_units * a.U;
 
   // queries pre-scaled by log2(e) / sqrt(D_h): S^T then holds exp2 arguments
   const float c = a.scale * 1.44269504088896341f;
@@ -118,10 +119,11 @@ __global__ __launch_bounds__(256, NQB == 2 ? 2 : 3) void attn_mfma_kernel(AttnAr
   };
 #pragma unroll
   for (int qb = 0; qb < NQB; ++qb) {
-    const T* qp = (const T*)a.q + qrow(qb) * ldq + n * 64 + 8 * lh;
+    // (the query buffer is chunk-major: 8 columns of all rows, 16 bytes each)
+    const T* qp = (const T*)a.q + ((int64_t)(n * 8 + lh) * q_rows + qrow(qb)) * 8;
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
-      const uint4 v = *reinterpret_cast<const uint4*>(qp + 16 * ks);
+      const uint4 v = *reinterpret_cast<const uint4*>(qp + 16 * ks * q_rows);
       const V raw = *reinterpret_cast<const V*>(&v);
       V qv;
 #pragma unroll

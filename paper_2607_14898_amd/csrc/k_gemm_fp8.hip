@@ -199,8 +199,7 @@ __global__ __launch_bounds__(C::NT, C::MIN_BLOCKS) void gemm_fp8_kernel(
 #pragma unroll
         for (int j = 0; j < FN; ++j) acc[i][j][r] *= rs;
       }
-    store_tile<EPI, _Float16, FM, FN, !(C::NW == 4 && C::MIN_BLOCKS == 1)>(ep, acc, r0, c0, M, N, lr, lk,
-                                                                          reinterpret_cast<float*>(lds));
+    store_tile<EPI, _Float16, FM, FN, !(C::NW == 4 && C::MIN_BLOCKS == 1)>(ep, acc, r0, c0, M, N, lr, lk);
   }
 }
 
