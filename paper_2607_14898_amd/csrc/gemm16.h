@@ -123,16 +123,16 @@ __global__ __launch_bounds__(C::NT, C::MIN_BLOCKS) void gemm_mfma_kernel(
   // stage refill between them, evenly spaced, in this order
   auto mfmas_dma = [&](int slot, int st, int kt, int j0) {
     if constexpr (C::IL) {
-      constexpr int NM = FM * FN, ND = Q / 2, EVERY = NM / ND;
-      static_assert(Q % 2 == 0 && NM % ND == 0, "DMA spacing");
+      constexpr int NM = FM * FN, ND = Q / 2;
+      static_assert(Q % 2 == 0 && ND <= NM, "DMA spacing");
 #pragma unroll
       for (int m = 0; m < NM; ++m) {
         const int i = m / FN, j = m % FN;
         acc[i][j] = kTransposed<EPI> ? Mfma<T>::run(fb[slot][j], fa[slot][i], acc[i][j])
                                      : Mfma<T>::run(fa[slot][i], fb[slot][j], acc[i][j]);
-        if (m % EVERY == EVERY - 1) {
+        if ((m + 1) * ND / NM != m * ND / NM) {
           __builtin_amdgcn_sched_barrier(0);
-          dma1(st, kt, j0 + m / EVERY);
+          dma1(st, kt, j0 + m * ND / NM);
           __builtin_amdgcn_sched_barrier(0);
         }
       }
@@ -226,17 +226,15 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Tile choice, measured on the 480p / 720p decoder shapes (random fp16 data).
-// - 256 x 256 tiles (8 waves of 128 x 64) read the fewest LDS and L2 bytes
-//   per flop and win wherever there are enough of them to fill the 256 CUs,
-//   except for residual-add epilogues behind a short K loop.
-// - When 192 x 128 tiles come to one nearly full wave (200-256 workgroups,
-//   the backbone's M = 3600 x N = 1536 projections), one workgroup per CU with
-//   6 stages in flight wins.
-// - When even 128 x 128 tiles leave CUs idle (480p backbone), each CU runs a
-//   single workgroup, so it gets 6 stages in flight.
-// - Otherwise 128 x 128 tiles with 3 stages, several workgroups per CU, so one
-//   workgroup's epilogue and barriers overlap another's MFMAs.
+// Tile choice, measured on the decoder's shapes at 480p, 720p and 1080p and the S,
+// B, L and XL widths (random fp16 data). 128 x 256 tiles (TileD), two workgroups
+// to a CU, let one workgroup's epilogue and pipeline fill run under the other's
+// MFMAs, and win wherever they come to at least two rounds of 512 or to one
+// nearly full round. us, 128 x 256 / what else serves that shape best:
+//   SwiGLU 14400 x 12288 x 1536 459 / 471 (256 x 256), 6400 x 8192 x 1024 103 /
+//   120, 1040 x 12288 x 1536 46 / 51; but 1560 x 12288 x 1536 (1.2 rounds) 65 / 64
+//   SiLU 14400 x 6144 x 1536 259 / 282, 6240 x 6144 x 1536 116 / 133
+//   residual add 14400 x 1536 x 6144 250 / 280, 32640 x 1536 x 1536 174 / 192
 template <typename T, int EPI>
 hipError_t dispatch_tiles(const GemmArgs& g, hipStream_t s) {
   auto tiles = [&](int bm, int bn) { return ((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn); };
@@ -248,43 +246,74 @@ hipError_t dispatch_tiles(const GemmArgs& g, hipStream_t s) {
   // 35 / 31; SwiGLU at 384 13 / 16, at 960 20 / 15.
   if constexpr (EPI == EPI_QKV) {
     if (tiles(32, 64) <= 640) return launch_direct<T, 2, 6, EPI>(g, s);
-    if (tiles(32, 64) <= 1600) return launch_small<T, SmallCfg<2, 2, 2, 2, 3>, EPI>(g, s);
+    if (tiles(32, 64) <= 1600) return launch_small<T, SmallCfg<2, 2, 1, 2, 2, 3>, EPI>(g, s);
   } else if constexpr (EPI == EPI_SWIGLU) {
     if (tiles(32, 64) <= 400) return launch_direct<T, 2, 6, EPI>(g, s);
   } else {
     if (tiles(32, 32) <= 500) return launch_direct<T, 1, 12, EPI>(g, s);
-    if (tiles(32, 32) <= 1000) return launch_small<T, SmallCfg<2, 2, 1, 4, 4>, EPI>(g, s);
+    if (tiles(32, 32) <= 1000) return launch_small<T, SmallCfg<2, 2, 1, 1, 4, 4>, EPI>(g, s);
   }
-  const bool short_rmw = EPI == EPI_RESID_ADD && g.K <= 2048;
-  if (tiles(256, 256) >= 160 && !short_rmw) {
-    // a SwiGLU projection of under two rounds of 256 x 256 tiles (the 480p
-    // backbone: 336 tiles, 1.3 rounds) runs faster as 128 x 128 tiles, several
-    // per CU (measured 1.8% per 480p chunk); so do the QKV and temporal-up
-    // projections of the 720p refinement input (456 and 360 tiles)
-    if (EPI == EPI_SWIGLU && tiles(256, 256) < 512) return launch_gemm<T, TileS, EPI>(g, s);
-    if ((EPI == EPI_QKV || EPI == EPI_TUP) && tiles(256, 256) < 512) return launch_gemm<T, TileS, EPI>(g, s);
-    // 256 x 192 tiles where their rounds of 256 CUs, weighted by tile area,
-    // are fewer than those of 256 x 256 tiles (for instance 342 -> 456 tiles,
-    // 2 -> 1.5 round-equivalents, for 14400 x 1536 outputs). Their 96-column
-    // wave blocks suit every epilogue but the paired SwiGLU and the QKV post
-    // step (one 64-column head vector per wave); the GELU epilogue's erf needs
-    // more registers than a 4-wave 256 x 192 tile leaves.
-    if constexpr (EPI != EPI_SWIGLU && EPI != EPI_QKV && EPI != EPI_STORE_GELU) {
-      const int rounds_l = (tiles(256, 256) + 255) / 256, rounds_w = (tiles(256, 192) + 255) / 256;
-      if (4 * rounds_w * 3 < 4 * rounds_l * 4) return launch_gemm<T, TileW, EPI>(g, s);
+  const int tl = tiles(256, 256), td = tiles(128, 256), tm = tiles(192, 128);
+  const bool d_round = td > 400 && td <= 512;  // one nearly full round, two per CU
+  if constexpr (EPI == EPI_STORE_F32) {
+    // the embedding's K loop is two stages: nothing but the store (3600 rows: 7.4
+    // us against 9.7 with 192 x 128 tiles, 8160 rows 10.8 / 19.0 with 256 x 192)
+    if (g.K <= 128) return launch_gemm<T, TileS, EPI>(g, s);
+  } else if constexpr (EPI == EPI_SWIGLU || EPI == EPI_QKV) {
+    // (QKV, 32640 / 8160 x 1920 x 1536: 196 / 204 us, 54 / 57)
+    if (td >= 1024 || d_round) return launch_gemm<T, TileD, EPI>(g, s);
+    if (tl >= 160) return launch_gemm<T, TileS, EPI>(g, s);
+  } else {
+    // one workgroup of 128 x 64 per CU (us, this / 128 x 128): residual adds 1040
+    // x 1536 x 6144 37 / 42, 1600 x 1024 x 4096 25 / 32; 1560 x 1536 x 6144, 312
+    // tiles, 53 / 44
+    if (tiles(128, 64) <= 256) return launch_gemm<T, TileH, EPI>(g, s);
+    // 128 x 192 tiles that make one nearly full round, two per CU: the pixel store
+    // of 14400 x 768 x 6144 134 / 142 us (a residual add would spill registers)
+    if constexpr (EPI == EPI_PIXEL || EPI == EPI_LINEAR_PIXEL)
+      if (const int te = tiles(128, 192); te > 400 && te <= 512) return launch_gemm<T, TileE, EPI>(g, s);
+    if ((EPI == EPI_STORE_SILU || EPI == EPI_STORE_ACT || EPI == EPI_STORE_GELU) && td >= 300)
+      return launch_gemm<T, TileD, EPI>(g, s);
+    // temporal upsampling of 3600 rows (696 tiles): 75 / 81 us; of 8160 rows 167 /
+    // 162 with the 256-row tiles below
+    if (EPI == EPI_TUP && td >= 512 && tl < 512) return launch_gemm<T, TileD, EPI>(g, s);
+    if constexpr (EPI == EPI_RESID_ADD) {
+      if (g.K <= 2048) {
+        if (td >= 1024) return launch_gemm<T, TileD, EPI>(g, s);
+      } else if (td >= 600 && tl * 10 < (tl + 255) / 256 * 256 * 9) {
+        // (256 x 256 tiles where their last round is nearly full: 21000 x 1536 x
+        // 6144, 498 tiles, 351 / 361 us)
+        return launch_gemm<T, TileD, EPI>(g, s);
+      }
     }
-    return launch_gemm<T, TileL, EPI>(g, s);
+    if (tl >= 160 && !(EPI == EPI_RESID_ADD && g.K <= 2048)) {
+      // 256 x 192 tiles where their rounds of 256 CUs, weighted by tile area, are
+      // fewer than those of 256 x 256 tiles (the GELU epilogue's erf needs more
+      // registers than a 4-wave 256 x 192 tile leaves)
+      if constexpr (EPI != EPI_STORE_GELU) {
+        const int rounds_l = (tl + 255) / 256, rounds_w = (tiles(256, 192) + 255) / 256;
+        if (4 * rounds_w * 3 < 4 * rounds_l * 4) return launch_gemm<T, TileW, EPI>(g, s);
+      }
+      return launch_gemm<T, TileL, EPI>(g, s);
+    }
+    if constexpr (EPI == EPI_RESID_ADD) {
+      // residual adds: 192 x 128 tiles with 4 stages (two workgroups per CU)
+      // behind a long K loop in one round, and wherever they fill most of one
+      // round of two per CU (396 tiles, the 480p refinement's: 37 / 43 us; at 272,
+      // 6400 x 1024 x 4096, 76 / 57)
+      if ((tm >= 200 && tm <= 256 && g.K > 2048) || (tm >= 340 && tm <= 512))
+        return launch_gemm<T, TileM4, EPI>(g, s);
+    }
   }
-  const int tm = tiles(192, 128);
-  if constexpr (EPI == EPI_RESID_ADD) {
-    // residual adds: 192 x 128 tiles with 4 stages (two workgroups per CU)
-    // behind a long K loop in one round, and wherever 192 x 128 tiles make one
-    // round of two per CU (257-512 tiles, the 480p refinement O projection)
-    if ((tm >= 200 && tm <= 256 && g.K > 2048) || (tm > 256 && tm <= 512))
-      return launch_gemm<T, TileM4, EPI>(g, s);
-  }
+  // 192 x 128 tiles in one nearly full round of one workgroup per CU (the 720p
+  // backbone's residual adds); where even 128 x 128 tiles leave CUs idle, each CU
+  // runs one workgroup, with 6 stages in flight (residual adds with 8 waves: 1560 x
+  // 1536 x 1536 15.1 / 16.2 us); otherwise 128 x 128 tiles, several per CU
   if (tm >= 200 && tm <= 256) return launch_gemm<T, TileM, EPI>(g, s);
-  if (tiles(128, 128) <= 256) return launch_gemm<T, TileS1, EPI>(g, s);
+  if (tiles(128, 128) <= 256) {
+    if constexpr (EPI == EPI_RESID_ADD) return launch_gemm<T, TileS8, EPI>(g, s);
+    else return launch_gemm<T, TileS1, EPI>(g, s);
+  }
   return launch_gemm<T, TileS, EPI>(g, s);
 }
 

@@ -27,18 +27,18 @@
 namespace fd {
 namespace {
 
-// Epilogue of one wave's 32 x 32 FN block.
-template <int EPI, typename T, int FN>
-__device__ __forceinline__ void store_small(const EpiParams& ep, const f32x16 (&acc)[1][FN], int r0, int c0, int M,
+// Epilogue of one wave's 32 FM x 32 FN block.
+template <int EPI, typename T, int FM, int FN>
+__device__ __forceinline__ void store_small(const EpiParams& ep, const f32x16 (&acc)[FM][FN], int r0, int c0, int M,
                                             int N, int lr, int lk, bool vec) {
   if constexpr (kTransposed<EPI>)
-    store_tile_t<EPI, T, 1, FN>(ep, acc, r0, c0, M, N, lr, lk, vec);
+    store_tile_t<EPI, T, FM, FN>(ep, acc, r0, c0, M, N, lr, lk, vec);
   else if constexpr (EPI == EPI_PIXEL || EPI == EPI_LINEAR_PIXEL) {
-    if (ep.out_fmt == 0) store_tile<EPI, T, 1, FN, true, 0>(ep, acc, r0, c0, M, N, lr, lk);
-    else if (ep.out_fmt == 1) store_tile<EPI, T, 1, FN, true, 1>(ep, acc, r0, c0, M, N, lr, lk);
-    else store_tile<EPI, T, 1, FN, true, 2>(ep, acc, r0, c0, M, N, lr, lk);
+    if (ep.out_fmt == 0) store_tile<EPI, T, FM, FN, true, 0>(ep, acc, r0, c0, M, N, lr, lk);
+    else if (ep.out_fmt == 1) store_tile<EPI, T, FM, FN, true, 1>(ep, acc, r0, c0, M, N, lr, lk);
+    else store_tile<EPI, T, FM, FN, true, 2>(ep, acc, r0, c0, M, N, lr, lk);
   } else {
-    store_tile<EPI, T, 1, FN, true>(ep, acc, r0, c0, M, N, lr, lk);
+    store_tile<EPI, T, FM, FN, true>(ep, acc, r0, c0, M, N, lr, lk);
   }
 }
 
@@ -104,15 +104,15 @@ __global__ __launch_bounds__(64, 1) void gemm_direct_kernel(const T* __restrict_
 #pragma unroll
   for (int p = 0; p < PD; ++p)
     if (base + p < KB) mul(p);
-  store_small<EPI, T, FN>(ep, acc, m0, n0, M, N, lr, lk, vec_store != 0);
+  store_small<EPI, T, 1, FN>(ep, acc, m0, n0, M, N, lr, lk, vec_store != 0);
 }
 
-// WAVES_M x WAVES_N waves of 32 x 32 FN; NS stages of KS 32-column K tiles.
-template <int WAVES_M_, int WAVES_N_, int FN_, int KS_, int NS_>
+// WAVES_M x WAVES_N waves of 32 FM x 32 FN; NS stages of KS 32-column K tiles.
+template <int WAVES_M_, int WAVES_N_, int FM_, int FN_, int KS_, int NS_>
 struct SmallCfg {
-  static constexpr int WAVES_M = WAVES_M_, WAVES_N = WAVES_N_, FN = FN_, KS = KS_, NS = NS_;
+  static constexpr int WAVES_M = WAVES_M_, WAVES_N = WAVES_N_, FM = FM_, FN = FN_, KS = KS_, NS = NS_;
   static constexpr int NW = WAVES_M * WAVES_N, NT = 64 * NW;
-  static constexpr int WN = 32 * FN, BM = 32 * WAVES_M, BN = WN * WAVES_N;
+  static constexpr int WM = 32 * FM, WN = 32 * FN, BM = WM * WAVES_M, BN = WN * WAVES_N;
   static constexpr int SUB = (BM + BN) * 4;   // 16-byte slots of a 32-column K tile
   static constexpr int STAGE = KS * SUB;
   static constexpr int QB16 = (BM + BN) / 16;            // 16-row blocks of a K tile
@@ -128,7 +128,7 @@ template <typename T, class C, int EPI>
 __global__ __launch_bounds__(C::NT, 1) void gemm_small_kernel(const T* __restrict__ A, const T* __restrict__ W, int M,
                                                               int N, int K, EpiParams ep, int tiles_m, int tiles_n,
                                                               int vec_store) {
-  constexpr int BM = C::BM, BN = C::BN, FN = C::FN, KS = C::KS, NS = C::NS, NW = C::NW, Q = C::Q;
+  constexpr int BM = C::BM, BN = C::BN, FM = C::FM, FN = C::FN, KS = C::KS, NS = C::NS, NW = C::NW, Q = C::Q;
   constexpr int NK = 2 * KS;  // MFMA k-steps of a stage
   using V = typename Mfma<T>::V;
   __shared__ uint4 lds[NS * C::STAGE];
@@ -138,7 +138,7 @@ __global__ __launch_bounds__(C::NT, 1) void gemm_small_kernel(const T* __restric
   int tm, tn;
   tile_of(blockIdx.x, tiles_m * tiles_n, tiles_m, tiles_n, tm, tn);
   const int m0 = tm * BM, n0 = tn * BN;
-  const int wm0 = (wave / C::WAVES_N) * 32, wn0 = (wave % C::WAVES_N) * C::WN;
+  const int wm0 = (wave / C::WAVES_N) * C::WM, wn0 = (wave % C::WAVES_N) * C::WN;
 
   const int KB = K / BKD;  // K tiles
   // 16-row blocks of this tile in A and W; the ragged edge of a tile rereads the
@@ -158,8 +158,9 @@ __global__ __launch_bounds__(C::NT, 1) void gemm_small_kernel(const T* __restric
       const int kt = min(t * KS + sub, KB - 1);
       const bool isA = blk < BM / 16;
       const int rb = isA ? min(blk, a_blk - 1) : min(blk - BM / 16, w_blk - 1);
-      const uint32_t soff = (uint32_t)(rb * KB + kt) * 1024u;
-      const uint32_t m0addr = lds0 + (uint32_t)(st * C::STAGE + sub * C::SUB + blk * 64) * 16u;
+      const uint32_t soff = __builtin_amdgcn_readfirstlane((uint32_t)(rb * KB + kt) * 1024u);
+      const uint32_t m0addr =
+          __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)(st * C::STAGE + sub * C::SUB + blk * 64) * 16u);
       const __amdgpu_buffer_rsrc_t r = isA ? rA : rB;
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
@@ -181,22 +182,27 @@ __global__ __launch_bounds__(C::NT, 1) void gemm_small_kernel(const T* __restric
     asm volatile("" ::: "memory");
   };
 
-  f32x16 acc[1][FN];
+  f32x16 acc[FM][FN];
 #pragma unroll
-  for (int j = 0; j < FN; ++j)
+  for (int i = 0; i < FM; ++i)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[0][j][r] = 0.f;
+    for (int j = 0; j < FN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
   const int lr = lane & 31, lk = lane >> 5;
   const int ia = (wm0 / 16 + (lr >> 4)) * 64 + (lr & 15), ib = ((BM + wn0) / 16 + (lr >> 4)) * 64 + (lr & 15);
-  V fa[2][NK], fb[2][NK][FN];
+  V fa[2][NK][FM], fb[2][NK][FN];
   auto load_frags = [&](int slot, int st) {
 #pragma unroll
     for (int ks = 0; ks < NK; ++ks) {
       const uint4* sb = lds + st * C::STAGE + (ks >> 1) * C::SUB;
       const int ch = (2 * (ks & 1) + lk) * 16;
-      const uint4 v = sb[ia + ch];
-      fa[slot][ks] = *reinterpret_cast<const V*>(&v);
+#pragma unroll
+      for (int i = 0; i < FM; ++i) {
+        const uint4 v = sb[ia + ch + i * 128];
+        fa[slot][ks][i] = *reinterpret_cast<const V*>(&v);
+      }
 #pragma unroll
       for (int j = 0; j < FN; ++j) {
         const uint4 w = sb[ib + ch + j * 128];
@@ -206,9 +212,11 @@ __global__ __launch_bounds__(C::NT, 1) void gemm_small_kernel(const T* __restric
   };
   auto mfma1 = [&](int slot, int ks) {
 #pragma unroll
-    for (int j = 0; j < FN; ++j)
-      acc[0][j] = kTransposed<EPI> ? Mfma<T>::run(fb[slot][ks][j], fa[slot][ks], acc[0][j])
-                                   : Mfma<T>::run(fa[slot][ks], fb[slot][ks][j], acc[0][j]);
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+        acc[i][j] = kTransposed<EPI> ? Mfma<T>::run(fb[slot][ks][j], fa[slot][ks][i], acc[i][j])
+                                     : Mfma<T>::run(fa[slot][ks][i], fb[slot][ks][j], acc[i][j]);
   };
 
   // Stage t sits in LDS stage t % NS and, while multiplied, in register set
@@ -247,7 +255,8 @@ __global__ __launch_bounds__(C::NT, 1) void gemm_small_kernel(const T* __restric
   if (t & 1) {
 #pragma unroll
     for (int ks = 0; ks < NK; ++ks) {
-      fa[0][ks] = fa[1][ks];
+#pragma unroll
+      for (int i = 0; i < FM; ++i) fa[0][ks][i] = fa[1][ks][i];
 #pragma unroll
       for (int j = 0; j < FN; ++j) fb[0][ks][j] = fb[1][ks][j];
     }
@@ -258,7 +267,7 @@ __global__ __launch_bounds__(C::NT, 1) void gemm_small_kernel(const T* __restric
       mfma1(0, 2 * sub);
       mfma1(0, 2 * sub + 1);
     }
-  store_small<EPI, T, FN>(ep, acc, m0 + wm0, n0 + wn0, M, N, lr, lk, vec_store != 0);
+  store_small<EPI, T, FM, FN>(ep, acc, m0 + wm0, n0 + wn0, M, N, lr, lk, vec_store != 0);
 }
 
 }  // namespace

@@ -682,10 +682,14 @@ template <int EPI> constexpr bool kTransposed = EPI == EPI_QKV || EPI == EPI_SWI
     EPI == EPI_STORE_ACT || EPI == EPI_STORE_SILU || EPI == EPI_STORE_GELU;
 
 using TileL = TileCfg<256, 256, 2, 4, 4, true>;   // 8 waves of 128 x 64, 128 KB LDS
+using TileD = TileCfg<128, 256, 1, 4, 3, true>;   // 4 waves of 128 x 64, 72 KB: two per CU
+using TileE = TileCfg<128, 192, 2, 2, 3>;         // 4 waves of 64 x 96, 60 KB: two per CU
 using TileW = TileCfg<256, 192, 2, 2, 5>;         // 4 waves of 128 x 96, 140 KB
 using TileM = TileCfg<192, 128, 2, 2, 6>;         // 4 waves of 96 x 64, 120 KB
 using TileM4 = TileCfg<192, 128, 2, 2, 4>;        // the same, 80 KB: two per CU
 using TileS1 = TileCfg<128, 128, 2, 2, 6, true>;  // 4 waves of 64 x 64, 96 KB
+using TileS8 = TileCfg<128, 128, 2, 4, 6, true>;  // 8 waves of 64 x 32, 96 KB
+using TileH = TileCfg<128, 64, 2, 2, 6>;          // 4 waves of 64 x 32, 72 KB
 using TileS = TileCfg<128, 128, 2, 2, 3, true>;   // 4 waves of 64 x 64, 48 KB
 
 }  // namespace
