@@ -263,13 +263,18 @@ __global__ __launch_bounds__(256, NQB == 2 ? 2 : 3) void attn_mfma_kernel(AttnAr
       // the padding keys of a unit's ragged last tile: register r of a lane
       // holds key 16 (r / 8) + 8 lh + r % 8 of its 32-key block
       if (tail) {
+        // (opaque to the compiler, which would otherwise keep 32 lane masks in
+        // scalar registers through the loop)
+        int first_pad = tail_valid;
+        asm volatile("" : "+s"(first_pad));
+        first_pad -= 8 * lh;
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
           for (int qb = 0; qb < NQB; ++qb)
 #pragma unroll
             for (int r = 0; r < 16; ++r)
-              if (kb * 32 + 16 * (r >> 3) + 8 * lh + (r & 7) >= tail_valid) s[kb][qb][r] = -INFINITY;
+              if (kb * 32 + 16 * (r >> 3) + (r & 7) >= first_pad) s[kb][qb][r] = -INFINITY;
       }
     };
     // P = exp2(S^T) in f16, laid out as the B operand of O^T += V^T P^T

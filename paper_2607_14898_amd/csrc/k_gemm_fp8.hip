@@ -95,11 +95,11 @@ __global__ __launch_bounds__(C::NT, C::MIN_BLOCKS) void gemm_fp8_kernel(
   // the two chunks of fragment row (A: wm0 + lr, W: BM + wn0 + lr): K-chunks 2 lk, 2 lk + 1
   const int ia0 = (wm0 + lr) * 4 + ((2 * lk) ^ xr), ia1 = (wm0 + lr) * 4 + ((2 * lk + 1) ^ xr);
   const int ib0 = (BM + wn0 + lr) * 4 + ((2 * lk) ^ xr), ib1 = (BM + wn0 + lr) * 4 + ((2 * lk + 1) ^ xr);
-  // 8-wave tiles leave 256 registers per lane: double-buffering both operands'
-  // fragments (96) beside 128 accumulators would spill, so the W fragments are
+  // Wave tiles of 128 x 64 leave too few registers for double-buffering both
+  // operands' fragments beside their accumulators, so the W fragments are
   // single-buffered there and each W block is re-read for the next tile as
   // soon as its last MFMA has issued.
-  constexpr bool FB1 = NW == 8;
+  constexpr bool FB1 = FM * FN >= 8;
   i32x8 fa[2][FM], fb[FB1 ? 1 : 2][FN];
   auto load_fa1 = [&](int slot, int st, int i) {
     const uint4* sb = lds + st * STAGE;
@@ -183,23 +183,23 @@ __global__ __launch_bounds__(C::NT, C::MIN_BLOCKS) void gemm_fp8_kernel(
   if constexpr (TR) {  // lane: row r0 + 32 i + lr; columns c0 + 32 j + 8 q + 4 lk + e
     store_tile_t<EPI, _Float16, FM, FN, true>(ep, acc, r0, c0, M, N, lr, lk, true);
   } else {  // lane: column c0 + 32 j + lr; rows r0 + 32 i + 8 (r / 4) + 4 lk + r % 4
+    float cs[FN];
 #pragma unroll
-    for (int j = 0; j < FN; ++j) {
-      const float cs = ep.col_scale[min(c0 + j * 32 + lr, N - 1)];
+    for (int j = 0; j < FN; ++j) cs[j] = ep.col_scale[min(c0 + j * 32 + lr, N - 1)];
+    // one 32-row block at a time: all blocks' row scales beside the accumulators
+    // would spill
 #pragma unroll
-      for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][j][r] *= cs;
-    }
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
+    for (int i = 0; i < FM; ++i) {
+      f32x16 blk[1][FN];
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const float rs = ep.row_scale[min(r0 + i * 32 + 8 * (r >> 2) + 4 * lk + (r & 3), M - 1) * ep.row_scale_stride];
 #pragma unroll
-        for (int j = 0; j < FN; ++j) acc[i][j][r] *= rs;
+        for (int j = 0; j < FN; ++j) blk[0][j][r] = acc[i][j][r] * cs[j] * rs;
       }
-    store_tile<EPI, _Float16, FM, FN, !(C::NW == 4 && C::MIN_BLOCKS == 1)>(ep, acc, r0, c0, M, N, lr, lk);
+      store_tile<EPI, _Float16, 1, FN, !(C::NW == 4 && C::MIN_BLOCKS == 1)>(ep, blk, r0 + i * 32, c0, M, N, lr, lk);
+      asm volatile("" ::: "memory");
+    }
   }
 }
 
@@ -211,15 +211,35 @@ hipError_t launch_fp8(const GemmArgs& g, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Tile choice of the E4M3 GEMM, measured on the decoder's shapes (us, this / the
+// 256 x 256, 192 x 128 or 3-stage 128 x 128 tiles in its place).
 template <int EPI>
 hipError_t dispatch_fp8(const GemmArgs& g, hipStream_t s) {
   auto tiles = [&](int bm, int bn) { return ((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn); };
-  // (256 x 256 tiles would spill the residual epilogue's registers)
-  if constexpr (EPI != EPI_RESID_ADD)
-    if (tiles(256, 256) >= 160) return launch_fp8<TileL, EPI>(g, s);
-  const int tm = tiles(192, 128);
-  if (tm >= 200) return launch_fp8<TileM, EPI>(g, s);
-  return launch_fp8<TileS, EPI>(g, s);
+  if constexpr (EPI == EPI_RESID_ADD) {
+    // 64 x 64 tiles while each CU holds one or two of them: 130 x 1536 x 6144 14.7 /
+    // 34.5, 520 x 1536 x 6144 15.7 / 35.2, 1600 x 1024 x 4096 14.7 / 21.1
+    const int t64 = tiles(64, 64), tm = tiles(192, 128);
+    if (t64 <= 256) return launch_fp8<TileCfg<64, 64, 2, 2, 8>, EPI>(g, s);
+    if (t64 <= 512) return launch_fp8<TileCfg<64, 64, 2, 2, 4>, EPI>(g, s);
+    // 8 waves of 64 x 32 on one 128 x 128 tile per CU: 1560 x 1536 x 6144 27.8 / 37.1
+    if (tiles(128, 128) <= 256) return launch_fp8<TileS8, EPI>(g, s);
+    // 192 x 128 tiles in one nearly full round of one per CU (3600 x 1536 x 6144
+    // 42.5 / 45.2 with 128 x 128), or in rounds of two per CU whose last is mostly
+    // full: 14400 x 1536 x 6144 133 / 176, 6240 x 1536 x 6144 65 / 85
+    if (tm >= 200 && tm <= 256) return launch_fp8<TileM, EPI>(g, s);
+    if (tm * 4 >= (tm + 511) / 512 * 512 * 3) return launch_fp8<TileM4, EPI>(g, s);
+    return launch_fp8<TileS, EPI>(g, s);
+  } else {
+    // 128 x 256 tiles, two per CU, as for the 16-bit GEMM: 14400 x 12288 x 1536 267 /
+    // 294, 6240 x 12288 x 1536 127 / 140; 64 x 128 tiles for the fewest rows: 60 x
+    // 12288 x 1536 9.7 / 12.9; 128 x 128 between: 1560 x 12288 x 1536 38 / 50, 520 x
+    // 12288 x 1536 18 / 30
+    const int td = tiles(128, 256);
+    if (td >= 1024 || (td > 400 && td <= 512)) return launch_fp8<TileD, EPI>(g, s);
+    if (tiles(64, 128) <= 500) return launch_fp8<TileCfg<64, 128, 2, 2, 4>, EPI>(g, s);
+    return launch_fp8<TileS, EPI>(g, s);
+  }
 }
 
 }  // namespace
