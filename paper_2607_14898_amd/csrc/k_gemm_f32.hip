@@ -153,13 +153,21 @@ template <int EPI>
 hipError_t launch_f32(const GemmArgs& g, hipStream_t s) {
   const bool vec = g.K % 4 == 0 && g.lda % 4 == 0 && g.ldw % 4 == 0 && (uintptr_t)g.A % 16 == 0 && (uintptr_t)g.W % 16 == 0;
   if (!vec) return launch_f32_tile<EPI, 2, false>(g, s);
+  // The F whose rounds of one workgroup per CU take the least time; a round's time
+  // for K = 1536 is 6, 13.4, 20 and 29 us for F = 1 to 4. Measured, us at F = 1 / 2 /
+  // 3 / 4: 130 x 1536 x 6144 86 / 46 / 67 / 99, 520 x 1536 x 6144 272 / 171 / 134 /
+  // 102, 1100 x 1536 x 1536 137 / 80 / 61 / 67, 512 x 128 x 512 5.2 / 6.6 / 10 / 13
   const int64_t no = EPI == EPI_SWIGLU ? g.N / 2 : g.N;
-  auto tiles = [&](int t) { return ((g.M + t - 1) / t) * ((no + t - 1) / t); };
-  // 64 x 64 tiles read the fewest bytes per flop; smaller ones where they would
-  // leave CUs idle
+  auto rounds = [&](int t) { return (((g.M + t - 1) / t) * ((no + t - 1) / t) + 255) / 256; };
+  const double us[4] = {6.0 * rounds(16), 13.4 * rounds(32), 20.0 * rounds(48),
+                        EPI == EPI_SWIGLU ? 1e30 : 29.0 * rounds(64)};  // (SwiGLU's two weight sets: F <= 3)
+  int f = 0;
+  for (int i = 1; i < 4; ++i)
+    if (us[i] < us[f]) f = i;
   if constexpr (EPI != EPI_SWIGLU)
-    if (tiles(64) >= 512) return launch_f32_tile<EPI, 4, true>(g, s);
-  if (tiles(32) >= 512) return launch_f32_tile<EPI, 2, true>(g, s);
+    if (f == 3) return launch_f32_tile<EPI, 4, true>(g, s);
+  if (f == 2) return launch_f32_tile<EPI, 3, true>(g, s);
+  if (f == 1) return launch_f32_tile<EPI, 2, true>(g, s);
   return launch_f32_tile<EPI, 1, true>(g, s);
 }
 

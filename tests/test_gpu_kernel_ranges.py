@@ -1,0 +1,96 @@
+"""The kernels' dispatch ranges, at the sizes where a tile rule changes or a
+remainder is left, through whole decodes.
+
+Every rule picks a kernel by the rows of the call, and every kernel computes an
+output element in the same order, so one call of several frames has to equal
+the calls of one frame bit for bit while the two take different kernels; against
+the oracle the usual tolerances hold (fp32: 1e-4 max-abs, 16-bit: 2e-2).
+"""
+from dataclasses import replace
+
+import numpy as np
+import pytest
+
+from oracle import decode_stream
+from paper_2607_14898_amd.workloads import MODELS, make_latents, make_weights
+
+from .gpu_util import run_decoder
+
+pytestmark = pytest.mark.gpu
+
+XL = replace(MODELS["xl-720p"], n_backbone_blocks=1, n_refine_blocks=1)
+S = replace(XL, latent_channels=48, patch=1, dim=512, n_heads=8, n_kv_groups=2, mlp_hidden=2048, head_hidden=2048)
+NARROW = replace(XL, dim=256, n_heads=4, n_kv_groups=2, mlp_hidden=1024, head_hidden=1024)
+
+
+# (model, latent grid, frames of the one call): token counts around the 16- and
+# 32-row block edges and the tile-count limits of the few-row kernels, and odd
+# units (value pairs that straddle a unit's end)
+CASES = [
+    ("xl-31", XL, 2, 62, 3),       # 31 tokens: one ragged 32-row tile, 3 frames: 93 rows
+    ("xl-33", XL, 6, 22, 2),       # 33 tokens: one row in the second tile
+    ("xl-130", XL, 20, 26, 4),     # 130 / 520 rows: direct and LDS tiles
+    ("xl-260", XL, 26, 40, 4),     # 260 / 1040 rows, 1040 / 4160 in refinement
+    ("s-195", replace(S, window=3), 13, 15, 3),
+    ("s-1001", S, 77, 13, 2),      # 1001 tokens: keys shared among workgroups
+    ("narrow-527", replace(NARROW, window=4), 34, 62, 2),
+]
+
+
+@pytest.mark.parametrize("name,model,lh,lw,frames", CASES, ids=[c[0] for c in CASES])
+@pytest.mark.parametrize("mlp", ["f16", "fp8"])
+def test_one_call_equals_single_frame_calls(name, model, lh, lw, frames, mlp):
+    m = replace(model, latent_h=lh, latent_w=lw, mlp_precision=mlp)
+    W = make_weights(m, 11)
+    z = make_latents(m, frames, 12)
+    one = run_decoder(m, W, z, frames)
+    each = run_decoder(m, W, z, 1, max_frames=frames)
+    assert np.isfinite(one).all()
+    np.testing.assert_array_equal(one, each)
+
+
+@pytest.mark.parametrize("name,model,lh,lw,frames", [CASES[0], CASES[1], CASES[4]], ids=["xl-31", "xl-33", "s-195"])
+@pytest.mark.parametrize("dtype", ["f16", "f32"])
+def test_small_ranges_match_the_oracle(name, model, lh, lw, frames, dtype):
+    m = replace(model, latent_h=lh, latent_w=lw, compute_dtype=dtype)
+    W = make_weights(m, 13)
+    z = make_latents(m, frames, 14)
+    got = run_decoder(m, W, z, frames)
+    ref = decode_stream(m, W, z, 1)
+    err = float(np.abs(got - ref).max())
+    print(f"{name} {dtype}: max-abs {err:.3e}")
+    assert err <= (1e-4 if dtype == "f32" else 2e-2)
+
+
+def test_split_keys_match_the_oracle():
+    """Few query tiles over a long walk of key tiles (1014 tokens, window 2: 32
+    workgroups, 32 key tiles): the keys are shared among workgroups and merged."""
+    m = replace(NARROW, latent_h=52, latent_w=78, n_refine_blocks=0)
+    W = make_weights(m, 15)
+    z = make_latents(m, 2, 16)
+    got = run_decoder(m, W, z, 1)
+    ref = decode_stream(m, W, z, 1)
+    assert float(np.abs(got - ref).max()) <= 2e-2
+
+
+# fp32 widths and token counts off every multiple: K tails of the 16-column
+# chunks (embedding inputs 12, MLP widths 70 and 68: with and without 16-byte rows),
+# D_h 16, 32 and 64, ragged query and key blocks
+F32 = [
+    (replace(MODELS["tiny"], latent_channels=12, latent_h=5, latent_w=7, mlp_hidden=68, head_hidden=70), 3),
+    (replace(MODELS["tiny"], latent_h=9, latent_w=11, n_heads=8, n_kv_groups=4, window=3), 4),
+    (replace(MODELS["tiny"], latent_h=3, latent_w=3, dim=256, n_heads=4, n_kv_groups=1, window=1), 2),
+    (replace(MODELS["tiny-asis"], latent_h=7, latent_w=9, window=2, mlp_hidden=70), 4),
+]
+
+
+@pytest.mark.parametrize("i", range(len(F32)))
+def test_fp32_remainders_match_the_oracle(i):
+    m, frames = F32[i]
+    W = make_weights(m, 17)
+    z = make_latents(m, frames, 18)
+    got = run_decoder(m, W, z, frames)
+    ref = decode_stream(m, W, z, m.unit_frames)
+    assert float(np.abs(got - ref).max()) <= 1e-4
+    each = run_decoder(m, W, z, m.unit_frames, max_frames=frames)
+    np.testing.assert_array_equal(got, each)
