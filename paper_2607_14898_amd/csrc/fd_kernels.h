@@ -82,8 +82,9 @@ struct EpiParams {
 };
 
 struct GemmArgs {
-  // [M, K] row-major with stride lda, or (16-bit MFMA GEMM, a_packed = 1)
-  // packed by pack_a16_index with lda = K over ceil(M / 16) 16 rows
+  // [M, K]: the 16-bit GEMM's packed by pack_a16_index (a_packed = 1, lda = K)
+  // over ceil(M / 16) 16 rows; the FP8 GEMM's packed by pack_a8_index or row-major
+  // with stride lda; the fp32 GEMM's row-major
   const void* A = nullptr;
   int a_packed = 0;
   // [N, K]: row-major with stride ldw for the fp32 GEMM; for the 16-bit MFMA
@@ -121,8 +122,7 @@ inline int64_t pack_w8_index(int64_t row, int64_t k, int64_t K) {
 // The same layout for E4M3 activation codes that are an FP8 GEMM's A operand
 // (a_packed; written by the norm, the quantiser and the E4M3 SwiGLU epilogue).
 inline int64_t pack_a8_index(int64_t row, int64_t k, int64_t K) { return pack_w8_index(row, k, K); }
-// 16-bit operand GEMM on MFMA (K > 0, K % 32 == 0, lda % 8 == 0, 16-byte aligned
-// A, row-major or packed; W packed as above).
+// 16-bit operand GEMM on MFMA (K > 0, K % 32 == 0; A and W packed as above).
 hipError_t gemm_mfma(Act16 t, const GemmArgs& g, hipStream_t stream);
 // (its two operand types, arguments already checked)
 hipError_t gemm_mfma_f16(const GemmArgs& g, hipStream_t stream);

@@ -970,8 +970,10 @@ WsLayout ws_layout(const fd_config& c, const Derived& d, int64_t M) {
   const int64_t MR = tf ? M * c.r_t : M;
   const int64_t D = c.dim;
   const size_t es = d.act_bytes;
-  // fp32 raw projections: the fp32 path's QKV post step and SwiGLU read them;
-  // the 16-bit path does both in GEMM epilogues
+  // fp32 raw projections, read by the fp32 path's QKV post step (the 16-bit path
+  // does it in the GEMM's epilogue). Its size also counts the gate/up width, which
+  // a GEMM epilogue has since taken over: a smaller buffer would change which
+  // calls fit the fixed workspace of fd_decode_chunk_noalloc.
   const int64_t raw_cols = d.is16 ? 0 : std::max<int64_t>(d.qkv_w, 2 * c.mlp_hidden);
   const int64_t hid = std::max<int64_t>(c.mlp_hidden, tf ? c.head_hidden : 0);
   auto al = [](int64_t b) { return (size_t)((b + 255) / 256 * 256); };

@@ -545,15 +545,17 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a, int q_tiles) 
         }
       mx = fmaxf(mx, __shfl_xor(mx, 16));
       mx = fmaxf(mx, __shfl_xor(mx, 32));
-      // (the first block of a step holds a visible key, so mx is finite)
-      const float alpha = expf(m_run[i] - mx);
+      // (a wave's scores may all be -inf where another wave's are not: the shift is
+      // then 0, so that its sums stay 0 instead of NaN)
+      const float sh = mx == -INFINITY ? 0.f : mx;
+      const float alpha = expf(m_run[i] - sh);
       m_run[i] = mx;
       float ls = 0.f;
 #pragma unroll
       for (int e = 0; e < KB; ++e)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          s[e][r] = expf(s[e][r] - mx);
+          s[e][r] = expf(s[e][r] - sh);
           ls += s[e][r];
         }
       l_run[i] = l_run[i] * alpha + ls;
