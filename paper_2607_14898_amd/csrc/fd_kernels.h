@@ -153,17 +153,7 @@ struct AttnArgs {
   int64_t u0 = 0;              // absolute index of the call's first unit
   int window = 1;              // W_frm in units
   float scale = 1.f;           // 1 / sqrt(D_h)
-  // 16-bit path: the keys of each query shared out among `splits` workgroups;
-  // each leaves an fp32 output in part [splits][N][16][rows][4] and its (shift,
-  // row sum) in part_ml [splits][N][rows], which a second kernel merges
-  int splits = 1;
-  float* part = nullptr;
-  float2* part_ml = nullptr;
 };
-// Into how many shares the 16-bit attention splits the keys (1: not at all).
-// Depends on the unit's size, the heads, the batch and the window, never on the
-// frames of the call, so a call of several frames equals the calls of one.
-int attention_splits(const AttnArgs& a, int64_t max_splits);
 hipError_t attention_mfma(Act16 t, const AttnArgs& a, hipStream_t stream);
 hipError_t attention_f32(const AttnArgs& a, hipStream_t stream);
 

@@ -520,16 +520,6 @@ fd_status run_stack(Ctx& x, const std::vector<LayerW>& layers, float* xs, int ro
     aa.window = c.window;
     aa.scale = 1.0f / std::sqrt((float)d.Dh);
     aa.o_packed = d.is16 ? 1 : 0;  // the O projection's A operand
-    if (d.is16) {
-      // room for split keys: the fp32 outputs in the MLP hidden's buffer, shifts
-      // and sums in the operand buffer (both free here), per row of this call
-      const int64_t rows_ratio = refine ? 1 : (c.head_kind == FD_HEAD_TEMPORAL_FIRST ? c.r_t : 1);
-      const int64_t hid = std::max<int64_t>(H, c.head_kind == FD_HEAD_TEMPORAL_FIRST ? c.head_hidden : 0);
-      const int64_t per_h = rows_ratio * hid * 2 / ((int64_t)D * 4), per_a = rows_ratio * D * 2 / ((int64_t)c.n_heads * 8);
-      aa.splits = fd::attention_splits(aa, std::min(per_h, per_a));
-      aa.part = (float*)kc->h;
-      aa.part_ml = (float2*)kc->a;
-    }
     double keys = 0.0;  // visible keys summed over the call's query units
     for (int lu = 0; lu < n_units; ++lu) {
       const int64_t u = u0 + lu;

@@ -25,7 +25,6 @@
 #include "fd_kernels.h"
 
 #include <hip/hip_bf16.h>
-#include <algorithm>
 #include <type_traits>
 
 namespace fd {
@@ -80,9 +79,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t attn_rsrc(const void* base, ui
 // they are copied there by buffer-to-LDS DMA (no register staging), one tile
 // ahead. Each wave's Q fragments sit in LDS too, which leaves the registers
 // for reading a whole tile's K fragments ahead of the score MFMAs.
-// SPLIT: the keys of a query tile are shared out among a.splits workgroups, each
-// leaving its unnormalised fp32 output, shift and row sum for attn_merge_kernel.
-template <typename T, int HPB, int NQB, bool SPLIT>
+template <typename T, int HPB, int NQB>
 __global__ __launch_bounds__(256, NQB == 2 ? 2 : 3) void attn_mfma_kernel(AttnArgs a, int q_tiles) {
   using M = AMfma<T>;
   using V = typename M::V;
@@ -105,9 +102,7 @@ __global__ __launch_bounds__(256, NQB == 2 ? 2 : 3) void attn_mfma_kernel(AttnAr
   const int xq = n_wg / 8, xr = n_wg % 8, xcd = lin % 8;
   const int wid = (xcd < xr ? xcd * (xq + 1) : xr * (xq + 1) + (xcd - xr) * xq) + lin / 8;
   const int bx = wid % nbx;
-  const int qt = bx % q_tiles;
-  const int bu_all = bx / q_tiles, bu = SPLIT ? bu_all % (a.n_units * a.B) : bu_all;
-  const int sp = SPLIT ? bu_all / (a.n_units * a.B) : 0;  // share of the keys
+  const int qt = bx % q_tiles, bu = bx / q_tiles;
   const int lu = bu % a.n_units, b = bu / a.n_units;
   const int head0 = (wid / nbx) * HPB;
   const int n = head0 + wave % HPB;
@@ -146,9 +141,7 @@ __global__ __launch_bounds__(256, NQB == 2 ? 2 : 3) void attn_mfma_kernel(AttnAr
   // tile and of the V^T tile; lane l lands in row base + l / 8, physical chunk
   // l % 8, which holds chunk (l % 8) ^ ((row / 2) % 8) (the swizzle of swz_k /
   // swz_v). The tile walk (ring slot, tile of the unit) advances incrementally.
-  // (a share of the keys starts at its own tile)
-  const int it0 = SPLIT ? n_it * sp / a.splits : 0, it1 = SPLIT ? n_it * (sp + 1) / a.splits : n_it;
-  int ld_kt = it0 % tiles_per_unit, ld_slot = (int)((u_lo + it0 / tiles_per_unit) % a.S);
+  int ld_slot = (int)(u_lo % a.S), ld_kt = 0;
   const int64_t ring0 = (int64_t)(b * a.G + g) * a.S;
   const __amdgpu_buffer_rsrc_t rk =
       attn_rsrc((const T*)a.k_ring + ring0 * a.U_pad * 64, (uint32_t)a.S * a.U_pad * 128u);
@@ -218,9 +211,9 @@ __global__ __launch_bounds__(256, NQB == 2 ? 2 : 3) void attn_mfma_kernel(AttnAr
 
   dma_tile(0);
   sync();
-  int kt = it0 % tiles_per_unit;
-  for (int it = it0; it < it1; ++it) {
-    const int cur = (it - it0) & 1;
+  int kt = 0;
+  for (int it = 0; it < n_it; ++it) {
+    const int cur = it & 1;
 
     // S^T = K Q^T - m_q: lane holds query lr of each 32-query block, 16 keys per key block
     const bool tail = kt == tiles_per_unit - 1 && tail_valid < KT;
@@ -249,7 +242,7 @@ __global__ __launch_bounds__(256, NQB == 2 ? 2 : 3) void attn_mfma_kernel(AttnAr
       // reads, still at the score block's priority, so their LDS latency
       // overlaps its issue (measured 1.3% faster per 720p chunk than at the
       // loop top)
-      if (with_dma && it + 1 < it1) dma_tile(cur ^ 1);
+      if (with_dma && it + 1 < n_it) dma_tile(cur ^ 1);
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -326,14 +319,14 @@ __global__ __launch_bounds__(256, NQB == 2 ? 2 : 3) void attn_mfma_kernel(AttnAr
     bool big = false;
 #pragma unroll
     for (int qb = 0; qb < NQB; ++qb) big = big || !(ls[qb] <= 32768.f);
-    if (it == it0 || __builtin_amdgcn_ballot_w64(big) != 0) {
+    if (it == 0 || __builtin_amdgcn_ballot_w64(big) != 0) {
       // On the first tile the shift of every query becomes that tile's max
       // (from the initial 0, so it also drops to a negative max: a row whose
       // logits all lie far below 0 would otherwise underflow to a zero sum);
       // later it is only ever raised. Softmax is invariant to the shift, so
       // any value that keeps P in f16 range is exact. The scores are
       // recomputed from the K tile still in LDS.
-      const bool first = it == it0;
+      const bool first = it == 0;
       scores(false);
 #pragma unroll
       for (int qb = 0; qb < NQB; ++qb) {
@@ -386,20 +379,6 @@ __global__ __launch_bounds__(256, NQB == 2 ? 2 : 3) void attn_mfma_kernel(AttnAr
 #pragma unroll
   for (int qb = 0; qb < NQB; ++qb) {
     const float l_tot = l_run[qb] + __shfl_xor(l_run[qb], 32);
-    if constexpr (SPLIT) {
-      if (q0 + qb * 32 + lr < a.U) {
-        const int64_t sn = (int64_t)sp * a.N + n;
-        float4* po = reinterpret_cast<float4*>(a.part) + (sn * 16 + lh) * q_rows + qrow(qb);
-#pragma unroll
-        for (int d = 0; d < 2; ++d)
-#pragma unroll
-          for (int r4 = 0; r4 < 4; ++r4)
-            po[(d * 8 + 2 * r4) * q_rows] = make_float4(acc[qb][d][r4 * 4], acc[qb][d][r4 * 4 + 1],
-                                                        acc[qb][d][r4 * 4 + 2], acc[qb][d][r4 * 4 + 3]);
-        if (lh == 0) a.part_ml[sn * q_rows + qrow(qb)] = make_float2(mq[qb], l_tot);
-      }
-      continue;
-    }
     const float inv = 1.f / l_tot;
     if (q0 + qb * 32 + lr < a.U) {
       // row-major, or the O projection's packed operand layout (blocks of 16
@@ -421,39 +400,6 @@ __global__ __launch_bounds__(256, NQB == 2 ? 2 : 3) void attn_mfma_kernel(AttnAr
         }
     }
   }
-}
-
-// Merges the shares of a split attention: O = sum_i 2^(m_i - m) O_i over
-// sum_i 2^(m_i - m) l_i, in the order of the shares, into the O projection's
-// packed operand layout. A thread takes 8 dimensions of one (row, head); rows run
-// along the lanes, so every access is contiguous.
-template <typename T>
-__global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a, int64_t rows) {
-  using M = AMfma<T>;
-  const int64_t row = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (row >= rows) return;
-  const int n = blockIdx.y >> 3, ch = blockIdx.y & 7;  // head, 8-column chunk
-  float m = -INFINITY;
-  for (int i = 0; i < a.splits; ++i) m = fmaxf(m, a.part_ml[((int64_t)i * a.N + n) * rows + row].x);
-  float o[8] = {}, l = 0.f;
-  for (int i = 0; i < a.splits; ++i) {
-    const int64_t sn = (int64_t)i * a.N + n;
-    const float2 ml = a.part_ml[sn * rows + row];
-    const float4* po = reinterpret_cast<const float4*>(a.part) + (sn * 16 + 2 * ch) * rows + row;
-    const float4 x = po[0], y = po[rows];
-    const float f = __builtin_amdgcn_exp2f(ml.x - m);
-    l = fmaf(f, ml.y, l);
-    const float v[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
-#pragma unroll
-    for (int e = 0; e < 8; ++e) o[e] = fmaf(f, v[e], o[e]);
-  }
-  const float inv = 1.f / l;
-  typedef typename M::E E;
-  E h[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) h[e] = M::cvt(o[e] * inv);
-  T* op = (T*)a.o + (row >> 4) * ((int64_t)a.N * 64) * 16 + (row & 15) * 8 + (int64_t)n * 1024 + (ch >> 2) * 512 + (ch & 3) * 128;
-  *reinterpret_cast<uint4*>(op) = *reinterpret_cast<const uint4*>(h);
 }
 
 // fp32 path (D_h = 16, 32 or 64) on the 16x16x4 fp32 MFMA: a workgroup is one
@@ -605,7 +551,7 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a, int q_tiles) 
 }  // namespace
 
 // Launch shape: 4 heads of a KV group per workgroup when the group has a
-// multiple of 4 query heads (GQA), and 32 queries per wave: 143 registers let
+// multiple of 4 query heads (GQA), and 32 queries per wave: 140 registers let
 // three workgroups share a CU (three waves per SIMD), which hides more of the
 // per-tile latency than 64 queries per wave (239 registers, two per CU) saves
 // in LDS reads and barriers (measured: 2509 vs 2550 us per 720p refinement
@@ -613,46 +559,15 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a, int q_tiles) 
 template <typename TT, int HPB>
 hipError_t attn_launch(const AttnArgs& a, hipStream_t s) {
   const int q_tiles = (a.U + 32 * (4 / HPB) - 1) / (32 * (4 / HPB));
-  if (a.splits > 1) {
-    const int64_t rows = (int64_t)a.B * a.n_units * a.U;
-    dim3 grid(q_tiles * a.n_units * a.B * a.splits, a.N / HPB);
-    hipLaunchKernelGGL((attn_mfma_kernel<TT, HPB, 1, true>), grid, dim3(256), 0, s, a, q_tiles);
-    hipLaunchKernelGGL((attn_merge_kernel<TT>), dim3((unsigned)((rows + 255) / 256), a.N * 8), dim3(256), 0, s, a, rows);
-    return hipGetLastError();
-  }
   dim3 grid(q_tiles * a.n_units * a.B, a.N / HPB);
-  hipLaunchKernelGGL((attn_mfma_kernel<TT, HPB, 1, false>), grid, dim3(256), 0, s, a, q_tiles);
+  hipLaunchKernelGGL((attn_mfma_kernel<TT, HPB, 1>), grid, dim3(256), 0, s, a, q_tiles);
   return hipGetLastError();
-}
-
-// Query heads of one KV group that share a workgroup.
-static int heads_per_block(const AttnArgs& a) {
-  const int hpg = a.N / a.G;
-  return hpg % 4 == 0 ? 4 : (hpg % 2 == 0 ? 2 : 1);
-}
-
-// A workgroup alone on its CU walks the key tiles at 0.75 us each, a chain that
-// three workgroups per CU hide (0.49 us per tile and CU); so where one unit's
-// query tiles leave CUs with one workgroup or none, two to four workgroups share
-// its keys. The merge pass costs 4 to 7 us, so the walk has to be long enough.
-// Measured, us unsplit / split (launch and merge; workgroups x key tiles): 98 x
-// 50 39 / 27 (4 shares), 147 x 50 40 / 32 (3), 196 x 50 39 / 37 (2), 294 x 50
-// 47 / 46, 294 x 100 92 / 77, 339 x 114 105 / 91, 378 x 64 64 / 62, 72 x 27 25 /
-// 17 (3); not worth it: 150 x 26 22 / 24, 210 x 36 29 / 32, 102 x 18 16 / 17.
-int attention_splits(const AttnArgs& a, int64_t max_splits) {
-  const int hpb = heads_per_block(a), q = 32 * (4 / hpb);
-  const int64_t wgs = (int64_t)((a.U + q - 1) / q) * a.B * (a.N / hpb);
-  const int64_t tiles = (int64_t)(a.U_pad / 64) * a.window;
-  if (wgs > 380 || tiles < (wgs <= 100 ? 24 : 40)) return 1;
-  int64_t s = std::min<int64_t>(4, std::max<int64_t>(2, (400 + wgs / 2) / wgs));
-  s = std::min({s, (int64_t)a.U_pad / 64, max_splits});  // (every share holds a tile, also in a first frame)
-  return s > 1 ? (int)s : 1;
 }
 
 hipError_t attention_mfma(Act16 t, const AttnArgs& a, hipStream_t s) {
   if (a.Dh != 64 || a.U <= 0 || a.U_pad % 64 || a.N % a.G) return hipErrorInvalidValue;
-  if (a.splits > 1 && (!a.o_packed || !a.part || !a.part_ml)) return hipErrorInvalidValue;
-  const int hpb = heads_per_block(a);
+  const int hpg = a.N / a.G;  // query heads per KV group
+  const int hpb = hpg % 4 == 0 ? 4 : (hpg % 2 == 0 ? 2 : 1);
   if (t == Act16::F16) {
     if (hpb == 4) return attn_launch<_Float16, 4>(a, s);
     if (hpb == 2) return attn_launch<_Float16, 2>(a, s);
