@@ -531,11 +531,11 @@ __device__ __forceinline__ void store_tile_t(const EpiParams& ep, const f32x16 (
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             float g = acc[i][j][4 * q + e], u = acc[i][j + 1][4 * q + e];
-            if (SCALED) {
-              g = g * sg[e] * rs[i];
-              u = u * su[e] * rs[i];
-            }
-            o4[e] = to_act<T>(sat16<T>(silu_f(g + bg[e]) * (u + bu[e]), nsat));
+            // (the row scale and the bias in one rounding, written out so that it
+            // is the same in every tile shape)
+            g = SCALED ? fmaf(g * sg[e], rs[i], bg[e]) : g + bg[e];
+            u = SCALED ? fmaf(u * su[e], rs[i], bu[e]) : u + bu[e];
+            o4[e] = to_act<T>(sat16<T>(silu_f(g) * u, nsat));
             h4[e] = (float)o4[e];
           }
           if constexpr (EPI == EPI_SWIGLU_E4M3) {

@@ -195,7 +195,13 @@ __global__ __launch_bounds__(C::NT, C::MIN_BLOCKS) void gemm_fp8_kernel(
       for (int r = 0; r < 16; ++r) {
         const float rs = ep.row_scale[min(r0 + i * 32 + 8 * (r >> 2) + 4 * lk + (r & 3), M - 1) * ep.row_scale_stride];
 #pragma unroll
-        for (int j = 0; j < FN; ++j) blk[0][j][r] = acc[i][j][r] * cs[j] * rs;
+        for (int j = 0; j < FN; ++j) {
+          // rounded before the bias is added: left to itself the compiler fuses
+          // the two in some tile shapes and not in others, and a row's result
+          // would depend on how many rows the call has
+#pragma clang fp contract(off)
+          blk[0][j][r] = acc[i][j][r] * cs[j] * rs;
+        }
       }
       store_tile<EPI, _Float16, 1, FN, !(C::NW == 4 && C::MIN_BLOCKS == 1)>(ep, blk, r0 + i * 32, c0, M, N, lr, lk);
       asm volatile("" ::: "memory");

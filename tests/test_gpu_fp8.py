@@ -251,6 +251,24 @@ def test_e4m3_gemm_full_size_refinement_shapes_sampled():
     _check_resid(a, sa, w, sw, b, 6144, rows=rows)
 
 
+@pytest.mark.parametrize("epilogue,N,rows", [
+    (0, 1536, (600, 1300, 2600, 3600, 5000, 6240)),   # residual add: a tile shape each
+    (1, 12288, (300, 1200, 1600, 3000)),              # SwiGLU
+], ids=["resid", "swiglu"])
+def test_e4m3_gemm_rows_do_not_depend_on_the_rows_of_the_call(epilogue, N, rows):
+    """Every tile shape gives a row the same bits: the first rows of a call equal
+    the call of those rows alone."""
+    K = 64
+    rng = np.random.default_rng(77)
+    a, sa, w, sw, b = _operands(rng, rows[-1], N, K)
+    out = (rng.standard_normal((rows[-1], N)).astype(np.float32) if epilogue == 0
+           else np.zeros((rows[-1], N // 2), np.float16))
+    whole = _run_gemm(a, sa, w, sw, b, K, epilogue, out)
+    for m in rows[:-1]:
+        got = _run_gemm(a[:m], sa[:m], w, sw, b, K, epilogue, out[:m])
+        assert np.array_equal(got, whole[:m]), f"{m} rows alone differ from the first {m} of {rows[-1]}"
+
+
 def test_e4m3_gemm_empty_call_is_a_no_op():
     import torch
     from paper_2607_14898_amd import flashdecoder as fdb
