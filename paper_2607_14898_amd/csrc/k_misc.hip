@@ -85,6 +85,13 @@ struct E4m3Row {
   }
 };
 
+// Sum of squares of a lane's four values of a row, written as the fused
+// multiply-adds it is: the order that the compiler picks by itself differs
+// between the norm's widths, and with it the last bit of a row's scale.
+__device__ __forceinline__ float sum_sq4(float x, float y, float z, float w) {
+  return fmaf(w, w, fmaf(z, z, fmaf(x, x, y * y)));
+}
+
 // One wave per row; rows of D floats (D % 4 == 0), NV = ceil(D / 256) float4 per
 // lane, all valid when FULL (D % 256 == 0; NV = 8 and FULL = false take any D up
 // to 2048). A row is one chain of load, wave reduction, store, so what a small
@@ -113,8 +120,7 @@ __global__ __launch_bounds__(256) void norm_kernel(const float* __restrict__ x, 
   }
 #pragma unroll
   for (int i = 0; i < NV; ++i) {
-    const float t = KIND == 0 ? v[i].x * v[i].x + v[i].y * v[i].y + v[i].z * v[i].z + v[i].w * v[i].w
-                              : v[i].x + v[i].y + v[i].z + v[i].w;
+    const float t = KIND == 0 ? sum_sq4(v[i].x, v[i].y, v[i].z, v[i].w) : v[i].x + v[i].y + v[i].z + v[i].w;
     if (FULL || lane + 64 * i < nv) s += t;
   }
   s = wave_sum(s);
@@ -126,8 +132,7 @@ __global__ __launch_bounds__(256) void norm_kernel(const float* __restrict__ x, 
     float q = 0.f;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-      const float a0 = v[i].x - mu, a1 = v[i].y - mu, a2 = v[i].z - mu, a3 = v[i].w - mu;
-      if (FULL || lane + 64 * i < nv) q += a0 * a0 + a1 * a1 + a2 * a2 + a3 * a3;
+      if (FULL || lane + 64 * i < nv) q += sum_sq4(v[i].x - mu, v[i].y - mu, v[i].z - mu, v[i].w - mu);
     }
     q = wave_sum(q);
     rs = rsqrtf(q / D + eps);

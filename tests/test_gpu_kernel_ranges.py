@@ -98,6 +98,40 @@ def test_streams_of_a_batch_equal_the_lone_streams(model, mlp):
         np.testing.assert_array_equal(both[b:b + 1], run_decoder(m, W, z[b:b + 1], 1))
 
 
+@pytest.mark.parametrize("dim", [64, 128, 256])
+def test_norm_rounds_alike_at_every_width(dim):
+    """A row repeated twice has the same RMS, and lanes that hold it twice add to
+    exactly twice its sum of squares, so the fp32 norm output of a width equals
+    that of the doubled width bit for bit: read as the amplitude of the FP8 MLP's
+    input, one row a call, over 64 rows."""
+    import torch
+    from paper_2607_14898_amd import flashdecoder as fdb
+    amax = []
+    for rep in (1, 2):
+        m = replace(NARROW, latent_h=1, latent_w=1, patch=1, dim=dim * rep, n_heads=dim * rep // 64, n_kv_groups=1,
+                    mlp_hidden=256, head_hidden=256, n_refine_blocks=0, window=1, mlp_precision="fp8")
+        W = make_weights(replace(m, dim=dim, n_heads=dim // 64), 23)
+        E = {k: (np.concatenate([v] * 2) if rep == 2 else v) for k, v in W.items()
+             if k in ("embed.w", "embed.b", "bb.0.norm2.g")}
+        W = {**make_weights(m, 24), **E}
+        for k in ("bb.0.wo", "bb.0.bo"):  # the attention adds nothing
+            W[k] = np.zeros_like(W[k])
+        dec = fdb.Decoder(m, W, max_batch=1, max_frames_per_call=1)
+        cache = fdb.KvCache(dec, 1)
+        z = torch.from_numpy(make_latents(m, 64, 25)).cuda()
+        out = torch.empty(dec.output_shape(1, 1), dtype=torch.float32, device="cuda")
+        rows = []
+        for t in range(64):
+            a = np.zeros(fdb.fd_fp8_act_count(dec.handle), np.float32)
+            fdb.fd_calibrate_chunk(dec.handle, z[:, :, t:t + 1].contiguous(), 1, cache.handle, out, a)
+            rows.append(a[0])
+        amax.append(np.array(rows))
+        cache.close()
+        dec.close()
+    assert (amax[0] > 0).all()
+    np.testing.assert_array_equal(amax[0], amax[1])
+
+
 # fp32 widths and token counts off every multiple: K tails of the 16-column
 # chunks (embedding inputs 12, MLP widths 70 and 68: with and without 16-byte rows),
 # D_h 16, 32 and 64, ragged query and key blocks
