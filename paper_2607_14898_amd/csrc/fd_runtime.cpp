@@ -952,6 +952,7 @@ fd_status upload_weights(fd_decoder* dec, const void* w, int32_t wdt, size_t n_e
 struct WsLayout {
   size_t xbb = 0, xrf = 0, raw = 0, a = 0, q = 0, o = 0, h = 0, u = 0, rt = 0, a8 = 0, h8 = 0, sa = 0,
          sh = 0, total = 0;
+  size_t noalloc = 0;  // what fd_decode_chunk_noalloc holds against its fixed array
   bool has_rf = false, has_raw = false, has_fp8 = false;
 };
 
@@ -961,10 +962,8 @@ WsLayout ws_layout(const fd_config& c, const Derived& d, int64_t M) {
   const int64_t D = c.dim;
   const size_t es = d.act_bytes;
   // fp32 raw projections, read by the fp32 path's QKV post step (the 16-bit path
-  // does it in the GEMM's epilogue). Its size also counts the gate/up width, which
-  // a GEMM epilogue has since taken over: a smaller buffer would change which
-  // calls fit the fixed workspace of fd_decode_chunk_noalloc.
-  const int64_t raw_cols = d.is16 ? 0 : std::max<int64_t>(d.qkv_w, 2 * c.mlp_hidden);
+  // does it in the GEMM's epilogue)
+  const int64_t raw_cols = d.is16 ? 0 : d.qkv_w;
   const int64_t hid = std::max<int64_t>(c.mlp_hidden, tf ? c.head_hidden : 0);
   auto al = [](int64_t b) { return (size_t)((b + 255) / 256 * 256); };
   // GEMM operands (a, o, h, u, a8, h8) in the packed layout hold whole 16-row blocks
@@ -991,6 +990,10 @@ WsLayout ws_layout(const fd_config& c, const Derived& d, int64_t M) {
     p += sizes[i];
   }
   w.total = p;
+  // the no-alloc call counts raw rows of the gate/up width as well (they held both
+  // before SwiGLU moved into the GEMM): which calls it takes stays what it was
+  const int64_t counted_cols = d.is16 ? 0 : std::max<int64_t>(d.qkv_w, 2 * c.mlp_hidden);
+  w.noalloc = p - al(MR * raw_cols * 4) + al(MR * counted_cols * 4);
   w.has_rf = tf;
   w.has_raw = raw_cols > 0;
   w.has_fp8 = d.mlp8;
@@ -1337,11 +1340,11 @@ fd_status fd_decode_chunk_noalloc(const fd_decoder* dec, const void* latent, int
   if (dec->d.mlp8s && !dec->act_set)
     return fail(FD_ERR_STATE, "static FP8 scales are not set (fd_set_fp8_act_amax)");
   const WsLayout w = ws_layout(dec->cfg, dec->d, (int64_t)cache->batch * n_frames * dec->d.L);
-  if (w.total > fd::kNoallocScratchBytes)
+  if (w.noalloc > fd::kNoallocScratchBytes)
     return fail(FD_ERR_UNSUPPORTED,
                 "this call needs %zu bytes of workspace; the fixed workspace of fd_decode_chunk_noalloc "
                 "holds %zu (fewer frames per call or a smaller batch fit)",
-                w.total, fd::kNoallocScratchBytes);
+                w.noalloc, fd::kNoallocScratchBytes);
   try {
     void* base = nullptr;
     const hipError_t e = fd::noalloc_scratch(dec->device, &base);

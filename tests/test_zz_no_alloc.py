@@ -72,3 +72,30 @@ def test_noalloc_decode_refuses_a_workspace_beyond_the_array():
     assert cache.position == 0
     cache.close()
     dec.close()
+
+
+def test_fp32_workspace_holds_no_gate_up_rows():
+    """fp32 XL widths, 720 tokens: the cache's device memory is that of the buffers
+    a decode uses (rows x D each for the residual streams, a, q and o, rows x 4 D
+    for the hidden values, rows x (D + 2 G D_h) for the raw QKV projection), while
+    the no-alloc call refuses this size as it always has."""
+    import torch
+    from paper_2607_14898_amd import flashdecoder as fdb
+    m = replace(MODELS["xl-720p"], latent_h=48, latent_w=60, n_backbone_blocks=0, n_refine_blocks=0,
+                compute_dtype="f32")
+    dec = fdb.Decoder(m, make_weights(m, 0), max_batch=1, max_frames_per_call=1)
+    z = torch.zeros((1, m.latent_channels, 1, m.latent_h, m.latent_w), device="cuda")
+    out = torch.empty(dec.output_shape(1, 1), dtype=torch.float32, device="cuda")
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    cache = fdb.KvCache(dec, 1)
+    used = free - torch.cuda.mem_get_info()[0]
+    rows = 720 * m.r_t
+    need = 4 * (720 * (m.dim + 64) + rows * (4 * m.dim + m.mlp_hidden + m.dim + 2 * m.n_kv_groups * 64))
+    print(f"cache {used / 2**20:.1f} MiB, buffers {need / 2**20:.1f} MiB", flush=True)
+    assert used <= need + (8 << 20)      # (the allocator's granularity)
+    with pytest.raises(fdb.FlashDecoderError) as ei:
+        fdb.fd_decode_chunk_noalloc(dec.handle, z, 1, cache.handle, out)
+    assert ei.value.status == fdb.FD_ERR_UNSUPPORTED and cache.position == 0
+    cache.close()
+    dec.close()
