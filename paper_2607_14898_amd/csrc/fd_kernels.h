@@ -7,6 +7,15 @@
 
 namespace fd {
 
+// Grid of a launch that numbers its workgroups in one row, as blockIdx.y *
+// gridDim.x + blockIdx.x (workgroups past `blocks` return): a launch takes fewer
+// than 2^32 work-items along a dimension, which 2^24 workgroups of 256 exceed.
+// (2^20 is a multiple of 8, so workgroup i stays on XCD i % 8.)
+inline dim3 row_grid(int64_t blocks) {
+  const int64_t x = blocks < (1 << 20) ? blocks : 1 << 20;
+  return dim3((unsigned)x, (unsigned)((blocks + x - 1) / x));
+}
+
 enum class Act16 : int { F16 = 0, BF16 = 1 };  // 16-bit MFMA operand format
 
 // GEMM epilogues: C = A W^T + bias, then one of these.

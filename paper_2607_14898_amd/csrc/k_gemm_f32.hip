@@ -31,8 +31,10 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 15, lg = lane >> 4;
+  const int bid = blockIdx.y * gridDim.x + blockIdx.x;
+  if (bid >= tiles_m * tiles_n) return;
   int tm, tn;
-  tile_of(blockIdx.x, tiles_m * tiles_n, tiles_m, tiles_n, tm, tn);
+  tile_of(bid, tiles_m * tiles_n, tiles_m, tiles_n, tm, tn);
   const int m0 = tm * T, n0 = tn * T;
   const int NO = SW ? N / 2 : N;  // output columns
   const float* pa[F];
@@ -144,7 +146,7 @@ template <int EPI, int F, bool VEC>
 hipError_t launch_f32_tile(const GemmArgs& g, hipStream_t s) {
   const int no = EPI == EPI_SWIGLU ? g.N / 2 : g.N;
   const int tm = (g.M + 16 * F - 1) / (16 * F), tn = (no + 16 * F - 1) / (16 * F);
-  hipLaunchKernelGGL((gemm_f32_kernel<EPI, F, VEC>), dim3(tm * tn), dim3(256), 0, s, (const float*)g.A,
+  hipLaunchKernelGGL((gemm_f32_kernel<EPI, F, VEC>), row_grid(tm * tn), dim3(256), 0, s, (const float*)g.A,
                      (const float*)g.W, g.M, g.N, g.K, g.lda, g.ldw, g.ep, tm, tn);
   return hipGetLastError();
 }

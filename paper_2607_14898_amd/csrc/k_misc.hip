@@ -256,7 +256,8 @@ __device__ __forceinline__ float2 rope_cs(const QkvPostArgs& a, int pair, int fs
 // (As two launches, the values with one 64-lane sum per row: 9 + 4 us at 130
 // rows, where a launch's latency is all there is.)
 constexpr int VP_ROWS = 64;
-__global__ __launch_bounds__(256) void qkv_post_kernel(QkvPostArgs a, int rows, int qk_blocks, int blocks_per_unit) {
+__global__ __launch_bounds__(256) void qkv_post_kernel(QkvPostArgs a, int rows, int qk_blocks, int v_blocks,
+                                                       int blocks_per_unit) {
   __shared__ float vt[64][VP_ROWS + 1];  // [dim][position]
   const int Dh = a.Dh, qpv = Dh / 4;  // threads per head vector
   const int width = a.N * Dh + 2 * a.G * Dh;
@@ -268,8 +269,10 @@ __global__ __launch_bounds__(256) void qkv_post_kernel(QkvPostArgs a, int rows, 
     const float4 gv = reinterpret_cast<const float4*>(gain)[qd];
     return make_float4(x.x * r * gv.x, x.y * r * gv.y, x.z * r * gv.z, x.w * r * gv.w);
   };
-  if ((int)blockIdx.x >= qk_blocks) {  // values
-    const int vb = blockIdx.x - qk_blocks;
+  const int bid = blockIdx.y * gridDim.x + blockIdx.x;
+  if (bid >= qk_blocks) {  // values
+    const int vb = bid - qk_blocks;
+    if (vb >= v_blocks) return;
     const int g = vb % a.G, blk = vb / a.G % blocks_per_unit, bu = vb / a.G / blocks_per_unit;
     const int units_per_batch = a.rows_per_batch / a.U;
     const int lu = bu % units_per_batch, b = bu / units_per_batch;
@@ -294,7 +297,7 @@ __global__ __launch_bounds__(256) void qkv_post_kernel(QkvPostArgs a, int rows, 
     return;
   }
   const int slots = a.N + a.G;
-  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t t = (int64_t)bid * 256 + threadIdx.x;
   const int64_t per_row = (int64_t)slots * qpv;
   const bool valid = t < (int64_t)rows * per_row;
   const int row = valid ? (int)(t / per_row) : 0;
@@ -483,9 +486,9 @@ hipError_t qkv_post(const QkvPostArgs& a, hipStream_t s) {
   const int64_t threads = (int64_t)rows * (a.N + a.G) * (a.Dh / 4);
   const int qk_blocks = (int)((threads + 255) / 256);
   const int blocks_per_unit = (a.U + VP_ROWS - 1) / VP_ROWS;
-  const int units = a.B * (a.rows_per_batch / a.U);
-  hipLaunchKernelGGL(qkv_post_kernel, dim3((unsigned)(qk_blocks + blocks_per_unit * units * a.G)), dim3(256), 0, s, a,
-                     rows, qk_blocks, blocks_per_unit);
+  const int v_blocks = blocks_per_unit * a.B * (a.rows_per_batch / a.U) * a.G;
+  hipLaunchKernelGGL(qkv_post_kernel, row_grid((int64_t)qk_blocks + v_blocks), dim3(256), 0, s, a, rows, qk_blocks,
+                     v_blocks, blocks_per_unit);
   return hipGetLastError();
 }
 

@@ -153,3 +153,28 @@ def test_fp32_remainders_match_the_oracle(i):
     assert float(np.abs(got - ref).max()) <= 1e-4
     each = run_decoder(m, W, z, m.unit_frames, max_frames=frames)
     np.testing.assert_array_equal(got, each)
+
+
+def test_fp32_gemm_of_more_than_2_24_tiles():
+    """An fp32 pixel head of 2 x 1,051,650 rows, 8192 columns and K = 2 (no 16-byte
+    rows): 16.8 M tiles of 32 x 32, 17 GB of uint8 pixels. The two frames in one
+    call equal the two calls of one frame, which launch half as many."""
+    import torch
+    from paper_2607_14898_amd import flashdecoder as fdb
+    m = replace(MODELS["tiny"], latent_channels=1, latent_h=1025, latent_w=1026, patch=1, dim=16, n_heads=1,
+                n_kv_groups=1, n_backbone_blocks=0, n_refine_blocks=0, mlp_hidden=2, head_hidden=2, r_t=1,
+                s_out=64, out_channels=2, window=1)
+    assert ((2 * 1025 * 1026 + 31) // 32) * (8192 // 32) > 2 ** 24
+    dec = fdb.Decoder(m, make_weights(m, 26, std=0.5), max_batch=1, max_frames_per_call=2)
+    cache = fdb.KvCache(dec, 1)
+    z = torch.from_numpy(make_latents(m, 2, 27)).cuda()
+    both = cache.decode_chunk(z, out_format=fdb.FD_PIXELS_U8)
+    torch.cuda.synchronize()
+    cache.reset()
+    for t in range(2):
+        one = cache.decode_chunk(z[:, :, t:t + 1].contiguous(), out_format=fdb.FD_PIXELS_U8)
+        assert torch.equal(both[:, :, t:t + 1], one)
+        assert one[..., :64].float().std() > 1
+        del one
+    cache.close()
+    dec.close()
