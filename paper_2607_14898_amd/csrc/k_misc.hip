@@ -178,7 +178,7 @@ __global__ __launch_bounds__(256) void quant_rows_kernel(const TIN* __restrict__
                                                          float* __restrict__ scale,
                                                          unsigned* __restrict__ amax_out, int packed) {
   const int lane = threadIdx.x & 63;
-  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int64_t row = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * 4 + (threadIdx.x >> 6);
   if (row >= M) return;
   const TIN* r = in + row * K;
   float amax = 0.f;
@@ -211,7 +211,7 @@ __global__ __launch_bounds__(256) void quant_rows16_kernel(const _Float16* __res
   typedef _Float16 h8 __attribute__((ext_vector_type(8)));
   constexpr int K = 512 * NV;
   const int lane = threadIdx.x & 63;
-  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int64_t row = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * 4 + (threadIdx.x >> 6);
   if (row >= M) return;
   const h8* r = reinterpret_cast<const h8*>(in + row * K);
   h8 v[NV];
@@ -454,10 +454,10 @@ hipError_t quant_rows_e4m3(const void* in, int in_kind, int64_t M, int K, uint8_
                            float* scale, hipStream_t s, unsigned* amax_out, bool packed) {
   if (M <= 0) return hipSuccess;
   if (K <= 0 || K % 8 || (in_kind != 0 && in_kind != 2) || (packed && K % 64)) return hipErrorInvalidValue;
-  const unsigned grid = (unsigned)((M + 3) / 4);
+  const dim3 grid = row_grid((M + 3) / 4);
   if (in_kind == 0 && (uintptr_t)in % 16 == 0 && (uintptr_t)codes % 8 == 0) {
     auto launch = [&](auto nv) {
-      hipLaunchKernelGGL((quant_rows16_kernel<decltype(nv)::value>), dim3(grid), dim3(256), 0, s, (const _Float16*)in, M,
+      hipLaunchKernelGGL((quant_rows16_kernel<decltype(nv)::value>), grid, dim3(256), 0, s, (const _Float16*)in, M,
                          codes, scale, amax_out, packed ? 1 : 0);
       return hipGetLastError();
     };
@@ -471,10 +471,10 @@ hipError_t quant_rows_e4m3(const void* in, int in_kind, int64_t M, int K, uint8_
     }
   }
   if (in_kind == 0)
-    hipLaunchKernelGGL(quant_rows_kernel<_Float16>, dim3(grid), dim3(256), 0, s, (const _Float16*)in, M,
+    hipLaunchKernelGGL(quant_rows_kernel<_Float16>, grid, dim3(256), 0, s, (const _Float16*)in, M,
                        K, codes, scale, amax_out, packed ? 1 : 0);
   else
-    hipLaunchKernelGGL(quant_rows_kernel<float>, dim3(grid), dim3(256), 0, s, (const float*)in, M, K,
+    hipLaunchKernelGGL(quant_rows_kernel<float>, grid, dim3(256), 0, s, (const float*)in, M, K,
                        codes, scale, amax_out, packed ? 1 : 0);
   return hipGetLastError();
 }

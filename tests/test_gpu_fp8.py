@@ -251,6 +251,23 @@ def test_e4m3_gemm_full_size_refinement_shapes_sampled():
     _check_resid(a, sa, w, sw, b, 6144, rows=rows)
 
 
+def test_device_e4m3_quantiser_takes_more_than_2_26_rows():
+    """2^26 + 4 rows of 8 (2^24 + 1 workgroups): the last rows, and some across the
+    range, as quantised alone."""
+    import torch
+    from paper_2607_14898_amd import flashdecoder as fdb
+    M = 2 ** 26 + 4
+    x = torch.randn((M, 8), device="cuda", generator=torch.Generator("cuda").manual_seed(3))
+    codes = torch.full((M, 8), 255, dtype=torch.uint8, device="cuda")
+    scales = torch.full((M,), -1.0, device="cuda")
+    fdb.fd_quantize_e4m3_rows_device(x, codes, scales)
+    for r0 in (0, 4096, M // 2, M - 64):
+        c, s = torch.empty((64, 8), dtype=torch.uint8, device="cuda"), torch.empty(64, device="cuda")
+        fdb.fd_quantize_e4m3_rows_device(x[r0:r0 + 64].contiguous(), c, s)
+        assert torch.equal(codes[r0:r0 + 64], c) and torch.equal(scales[r0:r0 + 64], s)
+    assert (scales > 0).all()
+
+
 @pytest.mark.parametrize("epilogue,N,rows", [
     (0, 1536, (600, 1300, 2600, 3600, 5000, 6240)),   # residual add: a tile shape each
     (1, 12288, (300, 1200, 1600, 3000)),              # SwiGLU
