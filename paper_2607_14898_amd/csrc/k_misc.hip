@@ -482,7 +482,8 @@ hipError_t quant_rows_e4m3(const void* in, int in_kind, int64_t M, int K, uint8_
 hipError_t qkv_post(const QkvPostArgs& a, hipStream_t s) {
   const int rows = a.B * a.rows_per_batch;
   if (rows <= 0) return hipSuccess;
-  if (a.Dh > 64 || a.Dh % 8 || a.rows_per_batch % a.U) return hipErrorInvalidValue;
+  // (a head vector is Dh / 4 lanes of a workgroup, which the sums halve)
+  if ((a.Dh != 16 && a.Dh != 32 && a.Dh != 64) || a.rows_per_batch % a.U) return hipErrorInvalidValue;
   const int64_t threads = (int64_t)rows * (a.N + a.G) * (a.Dh / 4);
   const int qk_blocks = (int)((threads + 255) / 256);
   const int blocks_per_unit = (a.U + VP_ROWS - 1) / VP_ROWS;

@@ -266,3 +266,26 @@ def test_sizes_beyond_the_kernels_ranges_are_refused(change):
     cfg = fdb.make_config(replace(MODELS["xl-720p"], **change))
     assert fdb.fd_config_validate(cfg) == fdb.FD_ERR_UNSUPPORTED
     assert lib.fd_last_error().decode() != ""
+
+
+def test_qkv_post_takes_the_head_dims_its_kernel_is_built_for():
+    """The fp32 QKV post step's sums halve the lanes of a head vector, so its
+    launcher refuses head dims other than 16, 32 and 64 by itself. (Where there is a
+    GPU a launcher that let one through would run on the null pointers.)"""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("for machines without a GPU")
+
+    class Args(ctypes.Structure):  # fd::QkvPostArgs
+        _fields_ = ([(n, ctypes.c_void_p) for n in ("raw", "q", "k_ring", "vt_ring", "knorm_g", "vnorm_g",
+                                                    "rope_axis", "rope_hw", "rope_t")] +
+                    [("rope", ctypes.c_int), ("eps", ctypes.c_float)] +
+                    [(n, ctypes.c_int) for n in ("B", "N", "G", "Dh", "rows_per_batch", "L", "grid_w", "U", "U_pad",
+                                                 "S")] +
+                    [("u0", ctypes.c_int64), ("out_kind", ctypes.c_int)])
+
+    post = _lib()._ZN2fd8qkv_postERKNS_11QkvPostArgsEP12ihipStream_t
+    invalid_value = 1  # hipErrorInvalidValue
+    for dh in (8, 16, 24, 32, 40, 48, 56, 64, 72):
+        a = Args(B=1, N=4, G=2, Dh=dh, rows_per_batch=64, L=64, grid_w=8, U=64, U_pad=64, S=1, out_kind=2)
+        assert (post(ctypes.byref(a), None) != invalid_value) == (dh in (16, 32, 64)), dh
