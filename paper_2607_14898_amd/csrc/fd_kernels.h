@@ -22,8 +22,7 @@ enum class Act16 : int { F16 = 0, BF16 = 1 };  // 16-bit MFMA operand format
 enum Epi : int {
   EPI_STORE_F32 = 0,   // out_f[row, col] = c
   EPI_RESID_ADD = 1,   // out_f[row, col] += c           (fp32 residual stream)
-  EPI_STORE_ACT = 2,   // out_a[row, col] = act(c)        (operand format of the next GEMM)
-  EPI_STORE_SILU = 3,  // out_a = SiLU(c)
+  EPI_STORE_SILU = 3,  // out_a[row, col] = SiLU(c)      (operand format of the next GEMM)
   EPI_STORE_GELU = 4,  // out_a = GELU(c), erf form
   EPI_SWIGLU = 5,      // out_a[row, j] = SiLU(c_gate) * c_up, W rows interleaved per 32
   EPI_TUP = 6,         // temporal upsampling reshape into the refinement stream (fp32)
@@ -32,7 +31,6 @@ enum Epi : int {
   EPI_QKV = 9,         // KV-norm + 3D-RoPE of the QKV projection: q buffer and K / V^T rings
   EPI_SWIGLU_E4M3 = 10,// SwiGLU as EPI_SWIGLU, rounded to fp16, then E4M3 codes at the static
                        // inverse scale out_scale[1] (FP8 GEMM only)
-  EPI_COUNT = 11
 };
 
 struct QkvPostArgs {
@@ -83,7 +81,7 @@ struct EpiParams {
   // fp16 SwiGLU / SiLU outputs beyond +-65504 are clamped to it; when set,
   // the number of clamped values is added here
   unsigned* sat = nullptr;
-  // 16-bit activation epilogues (EPI_STORE_ACT / _SILU / _GELU, EPI_SWIGLU of
+  // 16-bit activation epilogues (EPI_STORE_SILU / _GELU, EPI_SWIGLU of
   // the 16-bit GEMM) and the E4M3 SwiGLU codes of the FP8 GEMM: write out_a in
   // the packed operand layout (pack_a16_index / pack_a8_index with K = ld_out)
   // instead of row-major

@@ -373,9 +373,7 @@ fd_status run_gemm(Ctx& x, const fd::GemmArgs& g_in, double algo_k) {
     // attention outputs, the hidden of the activation epilogues) is stored in
     // the packed operand layout, and so is every 16-bit activation output.
     g.a_packed = 1;
-    if (g.epi == fd::EPI_SWIGLU || g.epi == fd::EPI_STORE_ACT || g.epi == fd::EPI_STORE_SILU ||
-        g.epi == fd::EPI_STORE_GELU)
-      g.ep.out_packed = 1;
+    if (g.epi == fd::EPI_SWIGLU || g.epi == fd::EPI_STORE_SILU || g.epi == fd::EPI_STORE_GELU) g.ep.out_packed = 1;
   }
   hipEvent_t ev;
   fd_status st = probe_begin(x.c, FD_KC_GEMM, x.s, &ev);

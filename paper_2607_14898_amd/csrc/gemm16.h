@@ -192,21 +192,17 @@ __global__ __launch_bounds__(C::NT, C::MIN_BLOCKS) void gemm_mfma_kernel(
   }
 }
 
-// Four consecutive output columns land contiguously and 16-byte aligned (fp32)
-// / 8-byte aligned (16-bit) in the destination.
-template <int EPI>
-bool vec_stores(const GemmArgs& g) {
-  bool vec = g.N % 4 == 0 && g.ep.ld_out % 4 == 0;
-  if (EPI == EPI_PIXEL || EPI == EPI_LINEAR_PIXEL) vec = vec && g.ep.s % 4 == 0;
-  if (EPI == EPI_TUP) vec = vec && g.ep.dim % 4 == 0;
-  return vec && ((uintptr_t)g.ep.out_f % 16 == 0) && ((uintptr_t)g.ep.out_a % 8 == 0);
+// Four consecutive columns of a 16-bit output land contiguously and 8-byte aligned
+// in the destination.
+inline bool vec_stores(const GemmArgs& g) {
+  return g.N % 4 == 0 && g.ep.ld_out % 4 == 0 && (uintptr_t)g.ep.out_a % 8 == 0;
 }
 
 template <typename T, int FN, int PD, int EPI>
 hipError_t launch_direct(const GemmArgs& g, hipStream_t s) {
   const int tm = (g.M + 31) / 32, tn = (g.N + 32 * FN - 1) / (32 * FN);
   hipLaunchKernelGGL((gemm_direct_kernel<T, FN, PD, EPI>), dim3(tm * tn), dim3(64), 0, s, (const T*)g.A,
-                     (const T*)g.W, g.M, g.N, g.K, g.ep, tm, tn, vec_stores<EPI>(g) ? 1 : 0);
+                     (const T*)g.W, g.M, g.N, g.K, g.ep, tm, tn, vec_stores(g) ? 1 : 0);
   return hipGetLastError();
 }
 
@@ -214,7 +210,7 @@ template <typename T, class C, int EPI>
 hipError_t launch_small(const GemmArgs& g, hipStream_t s) {
   const int tm = (g.M + C::BM - 1) / C::BM, tn = (g.N + C::BN - 1) / C::BN;
   hipLaunchKernelGGL((gemm_small_kernel<T, C, EPI>), dim3(tm * tn), dim3(C::NT), 0, s, (const T*)g.A, (const T*)g.W,
-                     g.M, g.N, g.K, g.ep, tm, tn, vec_stores<EPI>(g) ? 1 : 0);
+                     g.M, g.N, g.K, g.ep, tm, tn, vec_stores(g) ? 1 : 0);
   return hipGetLastError();
 }
 
@@ -222,7 +218,7 @@ template <typename T, class C, int EPI>
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
   const int tm = (g.M + C::BM - 1) / C::BM, tn = (g.N + C::BN - 1) / C::BN;
   hipLaunchKernelGGL((gemm_mfma_kernel<T, C, EPI>), dim3(tm * tn), dim3(C::NT), 0, s,
-                     (const T*)g.A, (const T*)g.W, g.M, g.N, g.K, g.ep, tm, tn, vec_stores<EPI>(g) ? 1 : 0);
+                     (const T*)g.A, (const T*)g.W, g.M, g.N, g.K, g.ep, tm, tn, vec_stores(g) ? 1 : 0);
   return hipGetLastError();
 }
 
@@ -272,7 +268,7 @@ hipError_t dispatch_tiles(const GemmArgs& g, hipStream_t s) {
     // of 14400 x 768 x 6144 134 / 142 us (a residual add would spill registers)
     if constexpr (EPI == EPI_PIXEL || EPI == EPI_LINEAR_PIXEL)
       if (const int te = tiles(128, 192); te > 400 && te <= 512) return launch_gemm<T, TileE, EPI>(g, s);
-    if ((EPI == EPI_STORE_SILU || EPI == EPI_STORE_ACT || EPI == EPI_STORE_GELU) && td >= 300)
+    if ((EPI == EPI_STORE_SILU || EPI == EPI_STORE_GELU) && td >= 300)
       return launch_gemm<T, TileD, EPI>(g, s);
     // temporal upsampling of 3600 rows (696 tiles): 75 / 81 us; of 8160 rows 167 /
     // 162 with the 256-row tiles below
@@ -322,7 +318,6 @@ hipError_t dispatch_epi(const GemmArgs& g, hipStream_t s) {
   switch (g.epi) {
     case EPI_STORE_F32: return dispatch_tiles<T, EPI_STORE_F32>(g, s);
     case EPI_RESID_ADD: return dispatch_tiles<T, EPI_RESID_ADD>(g, s);
-    case EPI_STORE_ACT: return dispatch_tiles<T, EPI_STORE_ACT>(g, s);
     case EPI_STORE_SILU: return dispatch_tiles<T, EPI_STORE_SILU>(g, s);
     case EPI_STORE_GELU: return dispatch_tiles<T, EPI_STORE_GELU>(g, s);
     case EPI_SWIGLU: return dispatch_tiles<T, EPI_SWIGLU>(g, s);

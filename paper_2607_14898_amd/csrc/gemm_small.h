@@ -172,14 +172,15 @@ __global__ __launch_bounds__(C::NT, 1) void gemm_small_kernel(const T* __restric
 #pragma clang diagnostic pop
     }
   };
-  // this wave's DMAs but the youngest `left` stages, and its LDS reads, are done;
-  // then the barrier publishes the stage and frees the one read before
+  // this wave's DMAs but those of the NS - 2 youngest stages (drain: all), and its
+  // LDS reads, are done; then the barrier publishes the stage and frees the one
+  // read before
   auto sync = [&](bool drain) {
     if (drain) __builtin_amdgcn_s_waitcnt(FD_VMCNT(0));
     else __builtin_amdgcn_s_waitcnt(FD_VMCNT((NS - 2) * Q));
     __builtin_amdgcn_s_waitcnt(FD_LGKMCNT0);
     asm volatile("" ::: "memory");
-    if constexpr (NW > 1) __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
   };
 

@@ -60,8 +60,7 @@ __device__ __forceinline__ void count_sat(unsigned* sat, int n) {
 // columns: row part (row / 16) 16 ld + (row % 16) 8, column part
 // (col / 32) 512 + (col % 32 / 8) 128 + col % 8).
 template <int EPI>
-constexpr bool kPackable = EPI == EPI_SWIGLU || EPI == EPI_STORE_ACT || EPI == EPI_STORE_SILU ||
-                           EPI == EPI_STORE_GELU;
+constexpr bool kPackable = EPI == EPI_SWIGLU || EPI == EPI_STORE_SILU || EPI == EPI_STORE_GELU;
 template <int EPI>
 __device__ __forceinline__ int64_t row_off(const EpiParams& p, int row) {
   if constexpr (EPI == EPI_TUP) {
@@ -131,25 +130,6 @@ __device__ __forceinline__ void px_store(const EpiParams& p, int64_t off, float 
   else if (f == 1) reinterpret_cast<__hip_bfloat16*>(p.out_f)[off] = __float2bfloat16(v);
   else reinterpret_cast<uint8_t*>(p.out_f)[off] = (uint8_t)px_u8(v);
 }
-// Four consecutive pixels at an offset that is a multiple of 4 (16-, 8- or
-// 4-byte store).
-template <int PXF>
-__device__ __forceinline__ void px_store4(const EpiParams& p, int64_t off, const float (&v)[4]) {
-  static_assert(PXF >= 0, "vector pixel stores take a compile-time format");
-  float c[4];
-#pragma unroll
-  for (int e = 0; e < 4; ++e) c[e] = px_clamp(p, v[e]);
-  if constexpr (PXF == 0) {
-    *reinterpret_cast<float4*>(p.out_f + off) = make_float4(c[0], c[1], c[2], c[3]);
-  } else if constexpr (PXF == 1) {  // packed from the bit patterns (no stack array)
-    auto bits = [](float x) { return (uint32_t)__bfloat16_as_ushort(__float2bfloat16(x)); };
-    *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(p.out_f) + off) =
-        make_uint2(bits(c[0]) | (bits(c[1]) << 16), bits(c[2]) | (bits(c[3]) << 16));
-  } else {
-    *reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(p.out_f) + off) =
-        px_u8(c[0]) | (px_u8(c[1]) << 8) | (px_u8(c[2]) << 16) | (px_u8(c[3]) << 24);
-  }
-}
 
 // Store one value (bias already added) at the precomputed offset.
 template <int EPI, typename TA, int PXF = -1>
@@ -158,8 +138,6 @@ __device__ __forceinline__ void epi_store(const EpiParams& p, int64_t off, float
     p.out_f[off] = c;
   } else if constexpr (EPI == EPI_RESID_ADD) {
     p.out_f[off] += c;
-  } else if constexpr (EPI == EPI_STORE_ACT) {
-    ((TA*)p.out_a)[off] = to_act<TA>(c);
   } else if constexpr (EPI == EPI_STORE_SILU) {
     ((TA*)p.out_a)[off] = to_act<TA>(silu_f(c));
   } else if constexpr (EPI == EPI_STORE_GELU) {
@@ -216,13 +194,6 @@ __device__ __forceinline__ void tile_of(int bid, int n_tiles, int tiles_m, int t
   tn = in / gm;
 }
 
-// Epilogue of one wave's FM x FN blocks of 32 x 32 accumulators whose first
-// output row / column are r0 / c0. MFMA accumulator layout: lane (lk, lr) holds
-// column lr of each block and rows 8 (r / 4) + 4 lk + r % 4 for r = 0..15.
-// Loads of the destination (residual add) are issued for a whole 32-row block
-// before any of its stores: interleaved, every load would wait for the store
-// before it (the compiler cannot tell the addresses apart) and each element
-// would cost a full memory round trip.
 // x / d for 0 <= x < 2^23 and 0 < d < 2^23, given inv = 1.0f / d (float product,
 // then one exact integer correction; the products fit 24 bits)
 __device__ __forceinline__ int div_small(int x, int d, float inv) {
@@ -231,108 +202,97 @@ __device__ __forceinline__ int div_small(int x, int d, float inv) {
   return q + (r >= d) - (r < 0);
 }
 
+// Epilogues with 16-bit destinations take the accumulators transposed: four
+// consecutive columns per lane make one 8-byte store and one bias / SiLU pass
+// per four values. fp32 destinations keep the direct layout, where the 32 lanes
+// of a half-wave write one full 128-byte row segment per store.
+template <int EPI> constexpr bool kTransposed = EPI == EPI_QKV || EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_E4M3 ||
+    EPI == EPI_STORE_SILU || EPI == EPI_STORE_GELU;
+
+// Epilogue of one wave's FM x FN blocks of 32 x 32 accumulators whose first
+// output row / column are r0 / c0. MFMA accumulator layout: lane (lk, lr) holds
+// column lr of each block and rows 8 (r / 4) + 4 lk + r % 4 for r = 0..15.
+// Loads of the destination (residual add) are issued for a whole 32-row block
+// before any of its stores: interleaved, every load would wait for the store
+// before it (the compiler cannot tell the addresses apart) and each element
+// would cost a full memory round trip.
 template <int EPI, typename T, int FM, int FN, bool FAST_RMW, int PXF = 0>
 __device__ __forceinline__ void store_tile(const EpiParams& ep, const f32x16 (&acc)[FM][FN], int r0,
                                            int c0, int M, int N, int lr, int lk) {
-  if constexpr (EPI == EPI_SWIGLU) {
-    float bg[FN / 2], bu[FN / 2];
+  int64_t coff[FN];
+  float cb[FN];
+  bool cok[FN];
 #pragma unroll
-    for (int j = 0; j < FN; j += 2) {
-      const int pc = min(c0 + j * 32 + lr, N - 33);  // packed gate column; up is +32
-      bg[j / 2] = ep.bias[pc];
-      bu[j / 2] = ep.bias[pc + 32];
+  for (int j = 0; j < FN; ++j) {
+    const int col = min(c0 + j * 32 + lr, N - 1);
+    coff[j] = col_off<EPI>(ep, col);
+    cb[j] = ep.bias[col];
+    cok[j] = c0 + j * 32 + lr < N;
+  }
+  // interior blocks (the wave's rows and columns all in range) skip the
+  // per-element checks; for the residual read-modify-write only where other
+  // waves of the CU cover its load latency (measured: slower on a lone
+  // 4-wave workgroup per CU)
+  const bool interior = (EPI != EPI_RESID_ADD || FAST_RMW) && r0 + FM * 32 <= M && c0 + FN * 32 <= N;
+#pragma unroll
+  for (int i = 0; i < FM; ++i) {
+    int64_t ro[16];
+    bool rok[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int row = r0 + i * 32 + 8 * (r >> 2) + 4 * lk + (r & 3);
+      rok[r] = row < M;
+      ro[r] = row_off<EPI>(ep, min(row, M - 1));
     }
+    if (interior) {
+      if constexpr (EPI == EPI_RESID_ADD || EPI == EPI_STORE_F32) {
+        // row-major destination: column blocks j are 32 floats apart, an
+        // immediate offset from one row pointer
+        float* rp[16];
 #pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = r0 + i * 32 + 8 * (r >> 2) + 4 * lk + (r & 3);
-        if (row >= M) continue;
-#pragma unroll
-        for (int j = 0; j < FN; j += 2) {
-          if (c0 + j * 32 + lr >= N) continue;
-          const float g = acc[i][j][r] + bg[j / 2];
-          const float u = acc[i][j + 1][r] + bu[j / 2];
-          const int oc = (c0 + j * 32) / 2 + lr;
-          ((T*)ep.out_a)[(int64_t)row * ep.ld_out + oc] = to_act<T>(silu_f(g) * u);
-        }
-      }
-  } else {
-    int64_t coff[FN];
-    float cb[FN];
-    bool cok[FN];
-#pragma unroll
-    for (int j = 0; j < FN; ++j) {
-      const int col = min(c0 + j * 32 + lr, N - 1);
-      coff[j] = col_off<EPI>(ep, col);
-      cb[j] = ep.bias[col];
-      cok[j] = c0 + j * 32 + lr < N;
-    }
-    // interior blocks (the wave's rows and columns all in range) skip the
-    // per-element checks; for the residual read-modify-write only where other
-    // waves of the CU cover its load latency (measured: slower on a lone
-    // 4-wave workgroup per CU)
-    const bool interior = (EPI != EPI_RESID_ADD || FAST_RMW) && r0 + FM * 32 <= M && c0 + FN * 32 <= N;
-#pragma unroll
-    for (int i = 0; i < FM; ++i) {
-      int64_t ro[16];
-      bool rok[16];
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = r0 + i * 32 + 8 * (r >> 2) + 4 * lk + (r & 3);
-        rok[r] = row < M;
-        ro[r] = row_off<EPI>(ep, min(row, M - 1));
-      }
-      if (interior) {
-        if constexpr (EPI == EPI_RESID_ADD || EPI == EPI_STORE_F32) {
-          // row-major destination: column blocks j are 32 floats apart, an
-          // immediate offset from one row pointer
-          float* rp[16];
+        for (int r = 0; r < 16; ++r)
+          rp[r] = ep.out_f + (int64_t)(r0 + i * 32 + 8 * (r >> 2) + 4 * lk + (r & 3)) * ep.ld_out + c0 + lr;
+        if constexpr (EPI == EPI_RESID_ADD) {
+          float old[16][FN];
 #pragma unroll
           for (int r = 0; r < 16; ++r)
-            rp[r] = ep.out_f + (int64_t)(r0 + i * 32 + 8 * (r >> 2) + 4 * lk + (r & 3)) * ep.ld_out + c0 + lr;
-          if constexpr (EPI == EPI_RESID_ADD) {
-            float old[16][FN];
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
+            for (int j = 0; j < FN; ++j) old[r][j] = rp[r][32 * j];
 #pragma unroll
-              for (int j = 0; j < FN; ++j) old[r][j] = rp[r][32 * j];
+          for (int r = 0; r < 16; ++r)
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
-#pragma unroll
-              for (int j = 0; j < FN; ++j) rp[r][32 * j] = old[r][j] + (acc[i][j][r] + cb[j]);
-          } else {
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-#pragma unroll
-              for (int j = 0; j < FN; ++j) rp[r][32 * j] = acc[i][j][r] + cb[j];
-          }
+            for (int j = 0; j < FN; ++j) rp[r][32 * j] = old[r][j] + (acc[i][j][r] + cb[j]);
         } else {
 #pragma unroll
           for (int r = 0; r < 16; ++r)
 #pragma unroll
-            for (int j = 0; j < FN; ++j) epi_store<EPI, T, PXF>(ep, ro[r] + coff[j], acc[i][j][r] + cb[j]);
+            for (int j = 0; j < FN; ++j) rp[r][32 * j] = acc[i][j][r] + cb[j];
         }
-        continue;
-      }
-      if constexpr (EPI == EPI_RESID_ADD) {
-        float old[16][FN];
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-#pragma unroll
-          for (int j = 0; j < FN; ++j) old[r][j] = rok[r] && cok[j] ? ep.out_f[ro[r] + coff[j]] : 0.f;
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-#pragma unroll
-          for (int j = 0; j < FN; ++j)
-            if (rok[r] && cok[j]) ep.out_f[ro[r] + coff[j]] = old[r][j] + (acc[i][j][r] + cb[j]);
       } else {
 #pragma unroll
         for (int r = 0; r < 16; ++r)
 #pragma unroll
-          for (int j = 0; j < FN; ++j)
-            if (rok[r] && cok[j]) epi_store<EPI, T, PXF>(ep, ro[r] + coff[j], acc[i][j][r] + cb[j]);
+          for (int j = 0; j < FN; ++j) epi_store<EPI, T, PXF>(ep, ro[r] + coff[j], acc[i][j][r] + cb[j]);
       }
+      continue;
+    }
+    if constexpr (EPI == EPI_RESID_ADD) {
+      float old[16][FN];
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) old[r][j] = rok[r] && cok[j] ? ep.out_f[ro[r] + coff[j]] : 0.f;
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+          if (rok[r] && cok[j]) ep.out_f[ro[r] + coff[j]] = old[r][j] + (acc[i][j][r] + cb[j]);
+    } else {
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+          if (rok[r] && cok[j]) epi_store<EPI, T, PXF>(ep, ro[r] + coff[j], acc[i][j][r] + cb[j]);
     }
   }
 }
@@ -478,16 +438,16 @@ __device__ __forceinline__ void store_qkv(const EpiParams& ep, const f32x16 (&ac
 // Epilogue of one wave's blocks computed transposed (acc[i][j] = W block j
 // times A block i): lane (lk, lr) holds output row r0 + 32 i + lr and, in
 // registers 4 q .. 4 q + 3, the four consecutive columns c0 + 32 j + 8 q +
-// 4 lk + 0..3. Every destination access covers those four columns at once (one
-// 16-byte fp32 or 8-byte 16-bit access) whenever the four land contiguously;
-// vec == false (a ragged or unaligned destination) stores element by element.
-template <int EPI, typename T, int FM, int FN, bool SCALED = false, int PXF = 0>
+// 4 lk + 0..3. Every store covers those four columns at once (8 bytes, or 4 of
+// E4M3 codes); vec == false (a ragged or unaligned SiLU / GELU destination) stores
+// element by element.
+template <int EPI, typename T, int FM, int FN, bool SCALED = false>
 __device__ __forceinline__ void store_tile_t(const EpiParams& ep, const f32x16 (&acc)[FM][FN], int r0,
                                              int c0, int M, int N, int lr, int lk, bool vec) {
   // SCALED (FP8 GEMM, SwiGLU only): each accumulator is multiplied by its
   // column's then its row's dequantisation scale right before use
-  static_assert(!SCALED || EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_E4M3, "scaled transposed epilogue: SwiGLU only");
-  typedef __attribute__((ext_vector_type(4))) float f4;
+  static_assert(kTransposed<EPI> && (!SCALED || EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_E4M3),
+                "epilogues with 16-bit or E4M3 destinations; scaled: SwiGLU only");
   if constexpr (EPI == EPI_QKV) {
     store_qkv<T, FM>(ep, acc, r0, c0, M, N, lr, lk);
     return;
@@ -582,55 +542,24 @@ __device__ __forceinline__ void store_tile_t(const EpiParams& ep, const f32x16 (
               if constexpr (EPI == EPI_STORE_SILU)
                 ((T*)ep.out_a)[ro[i] + col_off<EPI>(ep, n)] = to_act<T>(sat16<T>(silu_f(acc[i][j][4 * q + e] + cb[q][e]), nsat));
               else
-                epi_store<EPI, T, PXF>(ep, ro[i] + col_off<EPI>(ep, n), acc[i][j][4 * q + e] + cb[q][e]);
+                epi_store<EPI, T>(ep, ro[i] + col_off<EPI>(ep, n), acc[i][j][4 * q + e] + cb[q][e]);
             }
         continue;
       }
-      if constexpr (EPI == EPI_RESID_ADD) {
-        // the four loads of a row before its stores (the compiler cannot tell
-        // the addresses apart and would otherwise serialise each pair)
 #pragma unroll
-        for (int i = 0; i < FM; ++i) {
-          if (!rok[i]) continue;
-          f4 old[4];
+      for (int i = 0; i < FM; ++i)
 #pragma unroll
-          for (int q = 0; q < 4; ++q)
-            if (cok[q]) old[q] = *reinterpret_cast<const f4*>(ep.out_f + ro[i] + co[q]);
+        for (int q = 0; q < 4; ++q) {
+          if (!(rok[i] && cok[q])) continue;
+          T o4[4];
 #pragma unroll
-          for (int q = 0; q < 4; ++q)
-            if (cok[q]) {
-              f4 v;
-#pragma unroll
-              for (int e = 0; e < 4; ++e) v[e] = old[q][e] + (acc[i][j][4 * q + e] + cb[q][e]);
-              *reinterpret_cast<f4*>(ep.out_f + ro[i] + co[q]) = v;
-            }
-        }
-      } else {
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            if (!(rok[i] && cok[q])) continue;
-            float v[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = acc[i][j][4 * q + e] + cb[q][e];
-            const int64_t off = ro[i] + co[q];
-            if constexpr (EPI == EPI_STORE_F32 || EPI == EPI_TUP) {
-              *reinterpret_cast<f4*>(ep.out_f + off) = f4{v[0], v[1], v[2], v[3]};
-            } else if constexpr (EPI == EPI_PIXEL || EPI == EPI_LINEAR_PIXEL) {
-              px_store4<PXF>(ep, off, v);
-            } else {
-              T o4[4];
-#pragma unroll
-              for (int e = 0; e < 4; ++e) {
-                if constexpr (EPI == EPI_STORE_SILU) o4[e] = to_act<T>(sat16<T>(silu_f(v[e]), nsat));
-                else if constexpr (EPI == EPI_STORE_GELU) o4[e] = to_act<T>(gelu_f(v[e]));
-                else o4[e] = to_act<T>(v[e]);
-              }
-              *reinterpret_cast<uint2*>((T*)ep.out_a + off) = *reinterpret_cast<const uint2*>(o4);
-            }
+          for (int e = 0; e < 4; ++e) {
+            const float v = acc[i][j][4 * q + e] + cb[q][e];
+            if constexpr (EPI == EPI_STORE_SILU) o4[e] = to_act<T>(sat16<T>(silu_f(v), nsat));
+            else o4[e] = to_act<T>(gelu_f(v));
           }
-      }
+          *reinterpret_cast<uint2*>((T*)ep.out_a + ro[i] + co[q]) = *reinterpret_cast<const uint2*>(o4);
+        }
     }
   }
   if constexpr (EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_E4M3 || EPI == EPI_STORE_SILU) count_sat(ep.sat, nsat);
@@ -674,12 +603,6 @@ struct TileCfg {
 // so the compiler neither sees nor orders them; every ordering they need is
 // explicit: s_waitcnt on the wave's own DMAs, then s_barrier (with compiler
 // memory barriers around it) before any wave reads the tile or refills a stage.
-// Epilogues with 16-bit destinations take the accumulators transposed: four
-// consecutive columns per lane make one 8-byte store and one bias / SiLU pass
-// per four values. fp32 destinations keep the direct layout, where the 32 lanes
-// of a half-wave write one full 128-byte row segment per store.
-template <int EPI> constexpr bool kTransposed = EPI == EPI_QKV || EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_E4M3 ||
-    EPI == EPI_STORE_ACT || EPI == EPI_STORE_SILU || EPI == EPI_STORE_GELU;
 
 using TileL = TileCfg<256, 256, 2, 4, 4, true>;   // 8 waves of 128 x 64, 128 KB LDS
 using TileD = TileCfg<128, 256, 1, 4, 3, true>;   // 4 waves of 128 x 64, 72 KB: two per CU

@@ -8,8 +8,8 @@ constexpr int BKD = 32;  // K-columns per stage
 hipError_t gemm_mfma(Act16 t, const GemmArgs& g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
   if (g.K <= 0 || g.K % BKD || !g.a_packed || g.lda != g.K || g.ldw != g.K) return hipErrorInvalidValue;
-  if (g.ep.out_packed && (g.ep.ld_out % 32 || !(g.epi == EPI_SWIGLU || g.epi == EPI_STORE_ACT ||
-                                                g.epi == EPI_STORE_SILU || g.epi == EPI_STORE_GELU)))
+  if (g.ep.out_packed &&
+      (g.ep.ld_out % 32 || !(g.epi == EPI_SWIGLU || g.epi == EPI_STORE_SILU || g.epi == EPI_STORE_GELU)))
     return hipErrorInvalidValue;
   if ((g.epi == EPI_SWIGLU || g.epi == EPI_QKV) && g.N % 64) return hipErrorInvalidValue;
   if (g.epi == EPI_QKV && g.ep.qkv.Dh != 64) return hipErrorInvalidValue;

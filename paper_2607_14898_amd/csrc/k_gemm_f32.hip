@@ -181,7 +181,6 @@ hipError_t gemm_f32(const GemmArgs& g, hipStream_t s) {
   switch (g.epi) {
     case EPI_STORE_F32: return launch_f32<EPI_STORE_F32>(g, s);
     case EPI_RESID_ADD: return launch_f32<EPI_RESID_ADD>(g, s);
-    case EPI_STORE_ACT: return launch_f32<EPI_STORE_ACT>(g, s);
     case EPI_STORE_SILU: return launch_f32<EPI_STORE_SILU>(g, s);
     case EPI_STORE_GELU: return launch_f32<EPI_STORE_GELU>(g, s);
     case EPI_TUP: return launch_f32<EPI_TUP>(g, s);
