@@ -203,7 +203,8 @@ __global__ __launch_bounds__(256) void quant_rows_kernel(const TIN* __restrict__
 
 // The same for fp16 rows of 512 NV values held in registers: one pass over
 // memory, all of a row's loads in flight (1560 rows of 6144: 27 us with the two
-// passes above).
+// passes above). Built for the hidden widths (4 D) of the named decoder sizes;
+// other widths, for which nothing was measured, take the two passes.
 template <int NV>
 __global__ __launch_bounds__(256) void quant_rows16_kernel(const _Float16* __restrict__ in, int64_t M,
                                                            uint8_t* __restrict__ codes, float* __restrict__ scale,
