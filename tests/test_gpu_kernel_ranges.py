@@ -155,6 +155,41 @@ def test_fp32_remainders_match_the_oracle(i):
     np.testing.assert_array_equal(got, each)
 
 
+@pytest.mark.parametrize("batch", [1, 8], ids=["16-queries", "32-queries"])
+def test_fp32_attention_where_a_wave_sees_only_minus_infinity(batch):
+    """Four waves share a query tile's keys by 16-key blocks. Scores of some keys
+    overflow to -inf (q k = -1e40 in fp32): all of wave 1's, and the first four
+    blocks of wave 0, whose later blocks are finite. Those keys have weight 0, as in
+    the fp64 oracle, and nothing becomes NaN. The other keys' K is exactly 0: their
+    embeddings lie in pairs of opposite values in the other half of the channels, so
+    the LayerNorm leaves the first half at 0."""
+    m = replace(MODELS["tiny-asis"], latent_h=16, latent_w=16, n_backbone_blocks=1)  # 512 keys of 2 frames
+    D, dh = m.dim, m.dim // m.n_heads
+    W = make_weights(m, 28)
+    rng = np.random.default_rng(29)
+    sign = np.where(np.arange(D // 2) % 2, -1.0, 1.0).astype(np.float32)
+    E = np.zeros((D, m.latent_channels), np.float32)
+    E[:D // 2, 0] = sign
+    half = rng.standard_normal((D // 4, m.latent_channels - 1)).astype(np.float32)
+    E[D // 2::2, 1:], E[D // 2 + 1::2, 1:] = half, -half
+    qkv, b = W["bb.0.wqkv"].copy(), W["bb.0.bqkv"].copy()
+    qkv[:2 * D] = 0.0
+    b[:2 * D] = 0.0
+    b[:D:dh] = 1e20                                  # every query: 1e20 in its first channel
+    qkv[D:2 * D:dh, :D // 2] = -1e20 / (D // 2) * sign   # a marked token's key: about -1e20 there
+    W = {**W, "embed.w": E, "embed.b": np.zeros(D, np.float32), "bb.0.wqkv": qkv, "bb.0.bqkv": b,
+         "bb.0.norm1.g": np.ones(D, np.float32), "bb.0.norm1.b": np.zeros(D, np.float32)}
+    z = make_latents(m, 2, 30, batch=batch)
+    blk = (np.arange(512) // 16).reshape(2, 16, 16)  # key block of (frame, h, w)
+    marked = (blk % 4 == 1) | ((blk % 4 == 0) & (blk < 16))
+    z[:, 0] = marked
+    z[:, 1:] *= ~marked
+    got = run_decoder(m, W, z, 2)
+    ref = decode_stream(m, W, z, 2)
+    assert np.isfinite(got).all()
+    assert float(np.abs(got - ref).max()) <= 1e-4
+
+
 def test_fp32_gemm_of_more_than_2_24_tiles():
     """An fp32 pixel head of 2 x 1,051,650 rows, 8192 columns and K = 2 (no 16-byte
     rows): 16.8 M tiles of 32 x 32, 17 GB of uint8 pixels. The two frames in one
