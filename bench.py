@@ -160,14 +160,14 @@ def cpu_baselines() -> int:
 def trace_gaps(path: str, warmup: int, steps: int) -> int:
     """Idle time between the kernels of each timed decode call in a rocprofv3
     kernel trace (--kernel-trace --output-format csv) of this script run with
-    the same --warmup and --steps: per call, from the latent unshuffle to the
-    pixel-store GEMM, the wall span against the union of kernel intervals.
+    the same --warmup and --steps: per call, from the prologue (the latent
+    unshuffle) to the pixel-store GEMM, the wall span against the union of kernel intervals.
     Host-only; prints one JSON line."""
     import csv
     import numpy as np
     ks = sorted((int(r["Start_Timestamp"]), int(r["End_Timestamp"]), r["Kernel_Name"])
                 for r in csv.DictReader(open(path)))
-    starts = [i for i, k in enumerate(ks) if "unshuffle_kernel" in k[2]]
+    starts = [i for i, k in enumerate(ks) if "prologue_kernel" in k[2]]
     calls = []
     for a, b in zip(starts, starts[1:] + [len(ks)]):
         seg = ks[a:b]

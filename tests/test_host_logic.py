@@ -82,3 +82,26 @@ def test_every_workload_has_a_valid_shape():
         assert 0 <= w.pad_rows < m.latent_h
         if m.mlp_precision == "fp8s":
             assert min(w.fp8_amax) > 0
+
+
+def test_trace_gaps_finds_the_calls_of_a_kernel_trace(tmp_path, capsys):
+    """bench.py --trace-gaps tells the calls of a kernel trace by a call's first
+    kernel and its pixel-store GEMM: both exist under these names, and the idle
+    time of a trace of two calls (after one of warm-up) comes out."""
+    import json
+    import os
+    import bench
+    csrc = os.path.join(bench.ROOT, "paper_2607_14898_amd", "csrc")
+    assert "void prologue_kernel(" in open(os.path.join(csrc, "k_misc.hip")).read()
+    assert "EPI_PIXEL = 7," in open(os.path.join(csrc, "fd_kernels.h")).read()
+    rows, t = ["Kernel_Name,Start_Timestamp,End_Timestamp"], 0
+    for gap in (9000, 1000, 3000):
+        for name in ("fd::(anonymous namespace)::prologue_kernel(fd::RopeTimeArgs)",
+                     "_ZN2fd12_GLOBAL__N_116gemm_mfma_kernelIDF16_NS0_7TileCfgILi128ELi192EEELi7EEEvPKT_", "after_kernel"):
+            rows.append(f'"{name}",{t},{t + 5000}')
+            t += 5000 + gap
+    p = tmp_path / "t_kernel_trace.csv"
+    p.write_text("\n".join(rows) + "\n")
+    assert bench.trace_gaps(str(p), 1, 2) == 0
+    got = json.loads(capsys.readouterr().out)
+    assert (got["calls"], got["kernels_per_call"], got["span_us"], got["idle_us"]) == (2, 2.0, 12.0, 2.0)
