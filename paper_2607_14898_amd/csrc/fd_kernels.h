@@ -7,14 +7,11 @@
 
 namespace fd {
 
-// Grid of a launch that numbers its workgroups in one row, as blockIdx.y *
-// gridDim.x + blockIdx.x (workgroups past `blocks` return): a launch takes fewer
-// than 2^32 work-items along a dimension, which 2^24 workgroups of 256 exceed.
-// (2^20 is a multiple of 8, so workgroup i stays on XCD i % 8.)
-inline dim3 row_grid(int64_t blocks) {
-  const int64_t x = blocks < (1 << 20) ? blocks : 1 << 20;
-  return dim3((unsigned)x, (unsigned)((blocks + x - 1) / x));
-}
+// Workgroups of 256 in one launch, at most: a grid dimension holds fewer than 2^32
+// work-items, and a launch beyond that runs part of them without an error. Where
+// sizes can ask for more, the launcher makes several launches (a second grid
+// dimension instead cost small calls 1%).
+constexpr int kMaxLaunch = 1 << 23;
 
 enum class Act16 : int { F16 = 0, BF16 = 1 };  // 16-bit MFMA operand format
 

@@ -1,6 +1,8 @@
 // fp32 projections (fp32 compute path).
 #include "gemm_tile.h"
 
+#include <algorithm>
+
 namespace fd {
 namespace {
 
@@ -22,7 +24,7 @@ template <int EPI, int F, bool VEC>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A,
                                                        const float* __restrict__ W, int M, int N,
                                                        int K, int lda, int ldw, EpiParams ep,
-                                                       int tiles_m, int tiles_n) {
+                                                       int tiles_m, int tiles_n, int tile0) {
   constexpr bool SW = EPI == EPI_SWIGLU;
   constexpr int NB = SW ? 2 : 1;          // W row sets
   constexpr int PD = F == 1 ? 6 : (F == 2 ? 3 : 2);  // chunks in flight per wave
@@ -31,10 +33,8 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 15, lg = lane >> 4;
-  const int bid = blockIdx.y * gridDim.x + blockIdx.x;
-  if (bid >= tiles_m * tiles_n) return;
   int tm, tn;
-  tile_of(bid, tiles_m * tiles_n, tiles_m, tiles_n, tm, tn);
+  tile_of(blockIdx.x + tile0, tiles_m * tiles_n, tiles_m, tiles_n, tm, tn);
   const int m0 = tm * T, n0 = tn * T;
   const int NO = SW ? N / 2 : N;  // output columns
   const float* pa[F];
@@ -146,9 +146,13 @@ template <int EPI, int F, bool VEC>
 hipError_t launch_f32_tile(const GemmArgs& g, hipStream_t s) {
   const int no = EPI == EPI_SWIGLU ? g.N / 2 : g.N;
   const int tm = (g.M + 16 * F - 1) / (16 * F), tn = (no + 16 * F - 1) / (16 * F);
-  hipLaunchKernelGGL((gemm_f32_kernel<EPI, F, VEC>), row_grid(tm * tn), dim3(256), 0, s, (const float*)g.A,
-                     (const float*)g.W, g.M, g.N, g.K, g.lda, g.ldw, g.ep, tm, tn);
-  return hipGetLastError();
+  hipError_t e = hipSuccess;
+  for (int t0 = 0; t0 < tm * tn && e == hipSuccess; t0 += kMaxLaunch) {
+    hipLaunchKernelGGL((gemm_f32_kernel<EPI, F, VEC>), dim3(std::min(tm * tn - t0, kMaxLaunch)), dim3(256), 0, s,
+                       (const float*)g.A, (const float*)g.W, g.M, g.N, g.K, g.lda, g.ldw, g.ep, tm, tn, t0);
+    e = hipGetLastError();
+  }
+  return e;
 }
 
 template <int EPI>

@@ -13,6 +13,7 @@
 
 #include <hip/hip_bf16.h>
 
+#include <algorithm>
 #include <type_traits>
 
 namespace fd {
@@ -178,7 +179,7 @@ __global__ __launch_bounds__(256) void quant_rows_kernel(const TIN* __restrict__
                                                          float* __restrict__ scale,
                                                          unsigned* __restrict__ amax_out, int packed) {
   const int lane = threadIdx.x & 63;
-  const int64_t row = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * 4 + (threadIdx.x >> 6);
+  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= M) return;
   const TIN* r = in + row * K;
   float amax = 0.f;
@@ -212,7 +213,7 @@ __global__ __launch_bounds__(256) void quant_rows16_kernel(const _Float16* __res
   typedef _Float16 h8 __attribute__((ext_vector_type(8)));
   constexpr int K = 512 * NV;
   const int lane = threadIdx.x & 63;
-  const int64_t row = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * 4 + (threadIdx.x >> 6);
+  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= M) return;
   const h8* r = reinterpret_cast<const h8*>(in + row * K);
   h8 v[NV];
@@ -257,8 +258,8 @@ __device__ __forceinline__ float2 rope_cs(const QkvPostArgs& a, int pair, int fs
 // (As two launches, the values with one 64-lane sum per row: 9 + 4 us at 130
 // rows, where a launch's latency is all there is.)
 constexpr int VP_ROWS = 64;
-__global__ __launch_bounds__(256) void qkv_post_kernel(QkvPostArgs a, int rows, int qk_blocks, int v_blocks,
-                                                       int blocks_per_unit) {
+__global__ __launch_bounds__(256) void qkv_post_kernel(QkvPostArgs a, int rows, int qk_blocks, int blocks_per_unit,
+                                                       int block0) {
   __shared__ float vt[64][VP_ROWS + 1];  // [dim][position]
   const int Dh = a.Dh, qpv = Dh / 4;  // threads per head vector
   const int width = a.N * Dh + 2 * a.G * Dh;
@@ -270,10 +271,9 @@ __global__ __launch_bounds__(256) void qkv_post_kernel(QkvPostArgs a, int rows, 
     const float4 gv = reinterpret_cast<const float4*>(gain)[qd];
     return make_float4(x.x * r * gv.x, x.y * r * gv.y, x.z * r * gv.z, x.w * r * gv.w);
   };
-  const int bid = blockIdx.y * gridDim.x + blockIdx.x;
+  const int bid = blockIdx.x + block0;
   if (bid >= qk_blocks) {  // values
     const int vb = bid - qk_blocks;
-    if (vb >= v_blocks) return;
     const int g = vb % a.G, blk = vb / a.G % blocks_per_unit, bu = vb / a.G / blocks_per_unit;
     const int units_per_batch = a.rows_per_batch / a.U;
     const int lu = bu % units_per_batch, b = bu / units_per_batch;
@@ -455,7 +455,15 @@ hipError_t quant_rows_e4m3(const void* in, int in_kind, int64_t M, int K, uint8_
                            float* scale, hipStream_t s, unsigned* amax_out, bool packed) {
   if (M <= 0) return hipSuccess;
   if (K <= 0 || K % 8 || (in_kind != 0 && in_kind != 2) || (packed && K % 64)) return hipErrorInvalidValue;
-  const dim3 grid = row_grid((M + 3) / 4);
+  constexpr int64_t most = (int64_t)4 * kMaxLaunch;  // rows of a launch (whole 16-row blocks)
+  for (; M > most; M -= most) {
+    const hipError_t e = quant_rows_e4m3(in, in_kind, most, K, codes, scale, s, amax_out, packed);
+    if (e != hipSuccess) return e;
+    in = (const char*)in + most * K * (in_kind == 0 ? 2 : 4);
+    codes += most * K;
+    scale += most;
+  }
+  const dim3 grid((unsigned)((M + 3) / 4));
   if (in_kind == 0 && (uintptr_t)in % 16 == 0 && (uintptr_t)codes % 8 == 0) {
     auto launch = [&](auto nv) {
       hipLaunchKernelGGL((quant_rows16_kernel<decltype(nv)::value>), grid, dim3(256), 0, s, (const _Float16*)in, M,
@@ -488,10 +496,14 @@ hipError_t qkv_post(const QkvPostArgs& a, hipStream_t s) {
   const int64_t threads = (int64_t)rows * (a.N + a.G) * (a.Dh / 4);
   const int qk_blocks = (int)((threads + 255) / 256);
   const int blocks_per_unit = (a.U + VP_ROWS - 1) / VP_ROWS;
-  const int v_blocks = blocks_per_unit * a.B * (a.rows_per_batch / a.U) * a.G;
-  hipLaunchKernelGGL(qkv_post_kernel, row_grid((int64_t)qk_blocks + v_blocks), dim3(256), 0, s, a, rows, qk_blocks,
-                     v_blocks, blocks_per_unit);
-  return hipGetLastError();
+  const int blocks = qk_blocks + blocks_per_unit * a.B * (a.rows_per_batch / a.U) * a.G;
+  hipError_t e = hipSuccess;
+  for (int b0 = 0; b0 < blocks && e == hipSuccess; b0 += kMaxLaunch) {
+    hipLaunchKernelGGL(qkv_post_kernel, dim3(std::min(blocks - b0, kMaxLaunch)), dim3(256), 0, s, a, rows, qk_blocks,
+                       blocks_per_unit, b0);
+    e = hipGetLastError();
+  }
+  return e;
 }
 
 hipError_t prologue(const void* z, int z_kind, int B, int C, int F, int H, int W, int p, int K_pad, void* u,
